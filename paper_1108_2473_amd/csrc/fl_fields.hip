@@ -32,7 +32,7 @@ __device__ __forceinline__ long long lex_of(const LatGeom &g, int x, int y, int 
 
 // --- layout conversion --------------------------------------------------
 __global__ void k_canon_to_eo(const double *__restrict__ canon, double2 *even, double2 *odd,
-                              LatGeom g, int nrhs)
+                              LatGeom g, int nrhs, long long rstride)
 {
     long long V = 2LL * g.Vh;
     long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
@@ -40,7 +40,7 @@ __global__ void k_canon_to_eo(const double *__restrict__ canon, double2 *even, d
     int rhs = (int)(id / V);
     long long s = id - (long long)rhs * V;
     LexSite ls = lex_site(g, s);
-    double2 *f = (ls.par ? odd : even) + (size_t)rhs * 12 * g.Vh;
+    double2 *f = (ls.par ? odd : even) + (size_t)rhs * rstride;
     const double *src = canon + (size_t)id * 24;
     double2 *p[12];
     double2 v[12];
@@ -53,7 +53,7 @@ __global__ void k_canon_to_eo(const double *__restrict__ canon, double2 *even, d
 }
 
 __global__ void k_eo_to_canon(const double2 *even, const double2 *odd, double *__restrict__ canon,
-                              LatGeom g, int nrhs)
+                              LatGeom g, int nrhs, long long rstride)
 {
     long long V = 2LL * g.Vh;
     long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x;
@@ -61,7 +61,7 @@ __global__ void k_eo_to_canon(const double2 *even, const double2 *odd, double *_
     int rhs = (int)(id / V);
     long long s = id - (long long)rhs * V;
     LexSite ls = lex_site(g, s);
-    const double2 *f = (ls.par ? odd : even) + (size_t)rhs * 12 * g.Vh;
+    const double2 *f = (ls.par ? odd : even) + (size_t)rhs * rstride;
     double2 *dst = (double2 *)(canon + (size_t)id * 24);
     double2 *p[12];
     double2 v[12];
@@ -513,17 +513,19 @@ inline unsigned nblk(long long n, int b = 256) { return (unsigned)((n + b - 1) /
 }  // namespace
 
 void launch_canon_to_eo(const double *canon, double2 *even, double2 *odd, const LatGeom &g, int nrhs,
-                        hipStream_t s)
+                        hipStream_t s, long long rstride)
 {
     long long n = 2LL * g.Vh * nrhs;
-    if (n) hipLaunchKernelGGL(k_canon_to_eo, dim3(nblk(n)), dim3(256), 0, s, canon, even, odd, g, nrhs);
+    if (!rstride) rstride = 12LL * g.Vh;
+    if (n) hipLaunchKernelGGL(k_canon_to_eo, dim3(nblk(n)), dim3(256), 0, s, canon, even, odd, g, nrhs, rstride);
 }
 
 void launch_eo_to_canon(const double2 *even, const double2 *odd, double *canon, const LatGeom &g,
-                        int nrhs, hipStream_t s)
+                        int nrhs, hipStream_t s, long long rstride)
 {
     long long n = 2LL * g.Vh * nrhs;
-    if (n) hipLaunchKernelGGL(k_eo_to_canon, dim3(nblk(n)), dim3(256), 0, s, even, odd, canon, g, nrhs);
+    if (!rstride) rstride = 12LL * g.Vh;
+    if (n) hipLaunchKernelGGL(k_eo_to_canon, dim3(nblk(n)), dim3(256), 0, s, even, odd, canon, g, nrhs, rstride);
 }
 
 void launch_pack_links(const double *canon, void *dst, LinkFormat fmt, const LatGeom &g, hipStream_t s)

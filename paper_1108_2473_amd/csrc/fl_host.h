@@ -156,11 +156,12 @@ void launch_scalars(const ScalArgs &a, hipStream_t s);
 // ---------------------------------------------------------------------------
 // field kernels (layouts, sources, contractions, gradient)
 // ---------------------------------------------------------------------------
-// canonical double[n][V][4][3][2] <-> device (even, odd) FP64 fields
+// canonical double[n][V][4][3][2] <-> device (even, odd) FP64 fields; rstride:
+// values from one right-hand side to the next of even and of odd (0: 12 Vh)
 void launch_canon_to_eo(const double *canon, double2 *even, double2 *odd, const LatGeom &g,
-                        int nrhs, hipStream_t s);
+                        int nrhs, hipStream_t s, long long rstride = 0);
 void launch_eo_to_canon(const double2 *even, const double2 *odd, double *canon,
-                        const LatGeom &g, int nrhs, hipStream_t s);
+                        const LatGeom &g, int nrhs, hipStream_t s, long long rstride = 0);
 // canonical links double[4][V][3][3][2] -> [mu][par][NC][Vh] in the format fmt
 void launch_pack_links(const double *canon, void *dst, LinkFormat fmt, const LatGeom &g,
                        hipStream_t s);

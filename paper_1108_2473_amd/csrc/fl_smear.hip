@@ -27,9 +27,9 @@ constexpr int SM_RT = BLK / FL_WAVE;  // right-hand sides per smearing workgroup
 constexpr double kPi = 3.14159265358979323846;
 
 struct SmearArgs {
-    const double2 *same;   // input field of the output parity  [nrhs][12][Vh]
+    const double2 *same;   // input field of the output parity, 24 Vh values from field to field
     const double2 *other;  // input field of the other parity
-    double2 *out;          // output field                      [nrhs][12][Vh]
+    double2 *out;          // output field
     const double2 *gauge;  // FP64 18-real links [mu][par][9][Vh]
     LatGeom g;
     int nrhs, par;
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(BLK) void k_smear(SmearArgs a)
     const int sb = tile / nrg, rg = tile - sb * nrg;
     const int rhs = rg * SM_RT + (int)threadIdx.x / FL_WAVE, i = sb * FL_WAVE + (int)threadIdx.x % FL_WAVE;
     if (rhs >= a.nrhs || i >= g.Vh) return;
-    const size_t fs = (size_t)12 * g.Vh;
+    const size_t fs = (size_t)24 * g.Vh;
     const Coord c = cb_coords(g, a.par, i);
     cx<double> acc[12], psi[12], U[3][3];
     SpinorFmt<double>::load(a.same + rhs * fs, g.Vh, i, acc);
@@ -101,6 +101,190 @@ __global__ __launch_bounds__(BLK) void k_smear(SmearArgs a)
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = cx<double>{acc[k].re * a.inv_norm, acc[k].im * a.inv_norm};
     SpinorFmt<double>::store(a.out + rhs * fs, g.Vh, i, acc);
+}
+
+// ---------------------------------------------------------------------------
+// one step of (1 + alpha H) / norm on whole (x, y) planes, both parities in
+// one launch.  A thread owns one site and keeps its four links (U_x, U_y, U_z
+// of the site and U_z of the site below) in registers while its workgroup
+// goes through the spin components of the fields: H acts on colour only, so
+// every component meets the same links, which are read once per step instead
+// of once per field.  The x and y neighbours come through LDS (each site
+// leaves psi, U_x^+ psi and U_y^+ psi there), the two z neighbours from
+// memory, one component ahead of their use.  At 16^3x32 with 12 fields a step
+// takes 138 us for 660 MB that it cannot do without (4.8 TB/s; a copy reaches
+// 5.1): bound by memory.  Walking along z instead with every link reloaded per
+// pair of spins took 180 us, waiting for the links.
+// ---------------------------------------------------------------------------
+constexpr int PL_T = 256;    // threads of a plane workgroup, and the largest plane
+constexpr int PL_SLOT = 9;   // values of a thread's LDS slot (an odd stride in 16-byte units: no bank conflicts)
+
+struct PlaneArgs {
+    const double2 *in;     // [field][parity][12][Vh]
+    double2 *out;
+    const double2 *gauge;  // FP64 18-real links [mu][par][9][Vh]
+    LatGeom g;
+    int P;         // sites of a plane, Lx Ly
+    int npl;       // planes per workgroup
+    int nplanes;   // Lz Lt
+    int ncomp;     // spin components in all: 4 per field
+    int cc, nsplit;  // components per workgroup, workgroups per group of planes
+    double alpha, inv_norm;
+};
+
+// acc += M v, M = U or U^+ (one colour vector)
+template <bool ADJ>
+__device__ __forceinline__ void colour_mad(cx<double> acc[3], const cx<double> U[9], const cx<double> v[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) acc[a] = ADJ ? cjmad(acc[a], U[3 * b + a], v[b]) : cmad(acc[a], U[3 * a + b], v[b]);
+}
+
+// h = M v
+template <bool ADJ>
+__device__ __forceinline__ void colour_mul(cx<double> h[3], const cx<double> U[9], const cx<double> v[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        h[a] = ADJ ? cjmul(U[a], v[0]) : U[3 * a] * v[0];
+#pragma unroll
+        for (int b = 1; b < 3; ++b) h[a] = ADJ ? cjmad(h[a], U[3 * b + a], v[b]) : cmad(h[a], U[3 * a + b], v[b]);
+    }
+}
+
+// N components of stride cs bytes at byte offset voff
+template <int N>
+__device__ __forceinline__ void plane_load(const Buf &b, int voff, int soff, int cs, cx<double> s[N])
+{
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        const double2 v = v4f_to_d2(buf_ld16(b, voff, soff + c * cs));
+        s[c] = cx<double>{v.x, v.y};
+    }
+}
+
+// workgroup barrier for LDS traffic alone: loads and stores of device memory
+// stay in flight across it (__syncthreads waits for them as well)
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__global__ __launch_bounds__(PL_T, 2) void k_smear_plane(PlaneArgs a)
+{
+    extern __shared__ double2 lds[];  // [2][slot][psi, U_x^+ psi, U_y^+ psi of one spin component]
+    const LatGeom &g = a.g;
+    const int Vh = g.Vh, nslot = a.P * a.npl;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x, 0);
+    const int grp = tile / a.nsplit, part = tile - grp * a.nsplit;
+    const int tid = (int)threadIdx.x < nslot ? (int)threadIdx.x : 0;
+    int pl = tid / a.P;
+    const int s = tid - pl * a.P;
+    // a thread without a site of its own repeats the first plane's: it
+    // computes and stores the same values as their owner
+    if (grp * a.npl + pl >= a.nplanes) pl = 0;
+    const int slot = pl * a.P + s, plane = grp * a.npl + pl;
+    const int t = plane / g.L[2], z = plane - t * g.L[2];
+    // sites with x + y even come first, then the odd ones, each in
+    // checkerboard order: a wave's sites have one parity and its loads are
+    // contiguous
+    const int Lh0 = g.Lh0, Ly = g.L[1], Lz = g.L[2], hP = a.P >> 1;
+    const int hb = s >= hP ? 1 : 0, j = s - hb * hP;
+    const int y = j / Lh0, xh = j - y * Lh0, xo = (hb + y) & 1;
+    // slots of the plane neighbours, all in the other half
+    const int oth = slot + (hb ? -hP : hP);
+    const int sxf = oth + (xo ? (xh + 1 == Lh0 ? 1 - Lh0 : 1) : 0), sxb = oth + (xo ? 0 : (xh == 0 ? Lh0 - 1 : -1));
+    const int syf = oth + (y + 1 == Ly ? Lh0 - hP : Lh0), syb = oth + (y == 0 ? hP - Lh0 : -Lh0);
+    const int par = (hb + z + t) & 1;
+    // byte offsets: cs from component to component, ps from parity to parity
+    const int cs = Vh * 16, ps = 12 * cs, zs = hP * 16;
+    const int i = j * 16 + plane * zs, iu = i + (z + 1 == Lz ? zs - Lz * zs : zs), id = i + (z == 0 ? Lz * zs - zs : -zs);
+    const int own = par * ps + i, up = (1 - par) * ps + iu, dn = (1 - par) * ps + id;
+    cx<double> Ux[9], Uy[9], Uz[9], Ud[9];
+    {
+        const Buf gau = make_buf(a.gauge, 72u * (unsigned)cs);
+        plane_load<9>(gau, par * 9 * cs + i, 0, cs, Ux);
+        plane_load<9>(gau, par * 9 * cs + i, 18 * cs, cs, Uy);
+        plane_load<9>(gau, par * 9 * cs + i, 36 * cs, cs, Uz);
+        plane_load<9>(gau, (1 - par) * 9 * cs + id, 36 * cs, cs, Ud);
+    }
+    double2 *w = lds + PL_SLOT * slot;
+    const double2 *wxf = lds + PL_SLOT * sxf, *wxb = lds + PL_SLOT * sxb + 3;
+    const double2 *wyf = lds + PL_SLOT * syf, *wyb = lds + PL_SLOT * syb + 6;
+    const int hop = PL_SLOT * nslot;  // from one LDS buffer to the other
+    const int c0 = part * a.cc, c1 = min(c0 + a.cc, a.ncomp);
+    cx<double> cur[3], acc[3], nc[3], nu[3], nd[3];
+    v4f r[3] = {};
+    auto fetch = [&](int c) {
+        const Buf f = make_buf(a.in + (size_t)(c >> 2) * 24 * Vh, 2u * (unsigned)ps);
+        const int so = (c & 3) * 3 * cs;
+        plane_load<3>(f, own, so, cs, nc);
+        plane_load<3>(f, up, so, cs, nu);
+        plane_load<3>(f, dn, so, cs, nd);
+    };
+    // the z terms of the fetched component, and its plane terms left in LDS
+    auto enter = [&](int b) {
+        cx<double> h[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) cur[k] = nc[k];
+        colour_mul<false>(acc, Uz, nu);
+        colour_mad<true>(acc, Ud, nd);
+        double2 *q = w + b * hop;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q[k] = make_double2(cur[k].re, cur[k].im);
+        colour_mul<true>(h, Ux, cur);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q[3 + k] = make_double2(h[k].re, h[k].im);
+        colour_mul<true>(h, Uy, cur);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q[6 + k] = make_double2(h[k].re, h[k].im);
+    };
+    fetch(c0);
+    enter(c0 & 1);
+    for (int c = c0; c < c1; ++c) {
+        // the last component's result has left its registers (kept apart until here)
+        store_drain();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) asm volatile("" ::"v"(r[k]));
+        const bool more = c + 1 < c1;
+        if (more) fetch(c + 1);
+        lds_barrier();
+        const int b = (c & 1) * hop;
+        {
+            cx<double> q[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double2 u = wxf[b + k], d = wxb[b + k], e = wyb[b + k];
+                q[k] = cx<double>{u.x, u.y};
+                acc[k].re += d.x + e.x;
+                acc[k].im += d.y + e.y;
+            }
+            colour_mad<false>(acc, Ux, q);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const double2 u = wyf[b + k];
+                q[k] = cx<double>{u.x, u.y};
+            }
+            colour_mad<false>(acc, Uy, q);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            r[k] = d2_to_v4f(make_double2(fma(a.alpha, acc[k].re, cur[k].re) * a.inv_norm,
+                                          fma(a.alpha, acc[k].im, cur[k].im) * a.inv_norm));
+        const Buf f = make_buf(a.out + (size_t)(c >> 2) * 24 * Vh, 2u * (unsigned)ps);
+        store_fence_begin();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) buf_st16<ST_STREAM>(f, r[k], own, ((c & 3) * 3 + k) * cs);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) enter((c + 1) & 1);
+    }
+    store_drain();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) asm volatile("" ::"v"(r[k]));
 }
 
 // rho[s] = sum over right-hand sides and components of |phi|^2 at canonical site s
@@ -301,24 +485,55 @@ const double2 *smear_links(fl_ctx *c)
 // F^n on canonical fields in place (device), through checkerboard copies
 fl_status smear_canon(fl_ctx *c, double *canon, int nrhs, double alpha, int n, double norm)
 {
-    const size_t fb = (size_t)nrhs * c->Vh * 192;
-    double2 *e0 = (double2 *)ws_get(c, WS_SM_E0, fb), *o0 = (double2 *)ws_get(c, WS_SM_O0, fb);
-    double2 *e1 = (double2 *)ws_get(c, WS_SM_E1, fb), *o1 = (double2 *)ws_get(c, WS_SM_O1, fb);
+    const size_t fb = (size_t)nrhs * c->Vh * 384;
+    // fields as [nrhs][parity][12][Vh]
+    double2 *f0 = (double2 *)ws_get(c, WS_SM_E0, fb), *f1 = (double2 *)ws_get(c, WS_SM_E1, fb);
     const double2 *gauge = smear_links(c);
-    if (!e0 || !o0 || !e1 || !o1 || !gauge) return set_err(c, FL_ERR_NOMEM, "device allocation failed (smearing)");
+    if (!f0 || !f1 || !gauge) return set_err(c, FL_ERR_NOMEM, "device allocation failed (smearing)");
     LatGeom g = lat_geom(c, nrhs);
-    launch_canon_to_eo(canon, e0, o0, g, nrhs, c->stream);
-    // tiles of FL_WAVE sites x SM_RT right-hand sides
-    const unsigned nb = (unsigned)(((c->Vh + FL_WAVE - 1) / FL_WAVE) * (long long)((nrhs + SM_RT - 1) / SM_RT));
-    for (int k = 0; k < n; ++k) {
-        SmearArgs a{e0, o0, e1, gauge, g, nrhs, 0, alpha, 1.0 / norm};
-        hipLaunchKernelGGL(k_smear, dim3(nb), dim3(BLK), 0, c->stream, a);
-        SmearArgs b{o0, e0, o1, gauge, g, nrhs, 1, alpha, 1.0 / norm};
-        hipLaunchKernelGGL(k_smear, dim3(nb), dim3(BLK), 0, c->stream, b);
-        std::swap(e0, e1);
-        std::swap(o0, o1);
+    const long long odd = 12 * c->Vh, rs = 24 * c->Vh;
+    launch_canon_to_eo(canon, f0, f0 + odd, g, nrhs, c->stream, rs);
+    const int P = c->L[0] * c->L[1];
+    // planes of up to PL_T sites (16 x 16): the plane kernel, 138 us per step of
+    // 12 fields at 16^3x32 against 296 us of the gather kernel's two launches;
+    // 4^3x8, one field: 4 against 9 us.  Larger planes have no workgroup that
+    // holds them
+    const size_t shm = (size_t)2 * PL_SLOT * PL_T * sizeof(double2);
+    if (P <= PL_T && shm <= c->max_lds) {
+        PlaneArgs a;
+        a.gauge = gauge;
+        a.g = g;
+        a.P = P;
+        a.nplanes = c->L[2] * c->L[3];
+        a.npl = std::min(a.nplanes, PL_T / P);
+        a.alpha = alpha;
+        a.inv_norm = 1.0 / norm;
+        const int ngrp = (a.nplanes + a.npl - 1) / a.npl;
+        // two workgroups fit a CU: with fewer than 512 groups of planes the
+        // components are shared out over several workgroups of each
+        a.ncomp = 4 * nrhs;
+        a.nsplit = std::min(a.ncomp, std::max(1, 512 / ngrp));
+        a.cc = (a.ncomp + a.nsplit - 1) / a.nsplit;
+        a.nsplit = (a.ncomp + a.cc - 1) / a.cc;
+        const unsigned thr = (unsigned)((P * a.npl + FL_WAVE - 1) / FL_WAVE * FL_WAVE);
+        for (int k = 0; k < n; ++k) {
+            a.in = (k & 1) ? f1 : f0;
+            a.out = (k & 1) ? f0 : f1;
+            hipLaunchKernelGGL(k_smear_plane, dim3((unsigned)(ngrp * a.nsplit)), dim3(thr), shm, c->stream, a);
+        }
+        if (n & 1) std::swap(f0, f1);
+    } else {
+        // tiles of FL_WAVE sites x SM_RT right-hand sides
+        const unsigned nb = (unsigned)(((c->Vh + FL_WAVE - 1) / FL_WAVE) * (long long)((nrhs + SM_RT - 1) / SM_RT));
+        for (int k = 0; k < n; ++k) {
+            SmearArgs a{f0, f0 + odd, f1, gauge, g, nrhs, 0, alpha, 1.0 / norm};
+            hipLaunchKernelGGL(k_smear, dim3(nb), dim3(BLK), 0, c->stream, a);
+            SmearArgs b{f0 + odd, f0, f1 + odd, gauge, g, nrhs, 1, alpha, 1.0 / norm};
+            hipLaunchKernelGGL(k_smear, dim3(nb), dim3(BLK), 0, c->stream, b);
+            std::swap(f0, f1);
+        }
     }
-    launch_eo_to_canon(e0, o0, canon, g, nrhs, c->stream);
+    launch_eo_to_canon(f0, f0 + odd, canon, g, nrhs, c->stream, rs);
     return hip_check(c, hipGetLastError(), "smearing");
 }
 

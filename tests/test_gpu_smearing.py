@@ -29,6 +29,26 @@ def test_smearing_random_fields(F, dims, alpha, n, norm):
     lat.close()
 
 
+@pytest.mark.parametrize("dims,nrhs,n", [((16, 16, 2, 2), 1, 2),   # a whole workgroup per plane; one z neighbour twice
+                                         ((18, 16, 4, 2), 3, 3),   # planes larger than a workgroup
+                                         ((6, 10, 6, 2), 5, 1),    # four planes of 60 sites, idle threads
+                                         ((10, 4, 2, 6), 2, 4),    # six planes a workgroup, a part-filled last one
+                                         ((2, 2, 4, 2), 13, 3),    # every neighbour wraps; a second batch of one
+                                         ((16, 16, 16, 32), 1, 1)])  # several workgroups per plane
+def test_smearing_plane_shapes(F, dims, nrhs, n):
+    """Plane sizes around the workgroup size, planes per workgroup, splits of
+    the spin components and the kernel for larger planes, each an even and an
+    odd number of steps."""
+    U = S.random_links(dims, 0.5, 41)
+    psi = S.random_spinors(dims, nrhs, 42)
+    lat = F.Lattice(dims, -1)
+    lat.set_gauge(U)
+    got = lat.smear(psi, 1.5, n, 2.0)
+    want = O.smear(U, psi, dims, 1.5, n, 2.0)
+    assert np.abs(got - want).max() <= 1e-12 * np.abs(want).max()
+    lat.close()
+
+
 def test_smearing_device_in_place(F):
     import torch
     dims = (4, 4, 4, 8)
