@@ -245,9 +245,10 @@ void dispatch(const BlasArgs &a, dim3 grid, dim3 block, hipStream_t s)
 __device__ __forceinline__ bool finite_d(double v) { return v == v && v - v == 0.0; }
 
 // one step of a system's scalar recurrence on a local copy of its state
+template <int STEP>
 __device__ __forceinline__ void scal_step(const ScalArgs &a, const double P[6], SysState &s, int &act)
 {
-    switch (a.step) {
+    switch (STEP) {
     case SC_ALPHA: {
         double den = P[0] * P[0] + P[1] * P[1];
         if (!(den > 0) || !finite_d(den)) {
@@ -409,7 +410,7 @@ __device__ __forceinline__ void scal_step(const ScalArgs &a, const double P[6], 
 }
 
 // the partial-sum slots each scalar step reads (bit k: slot k)
-__device__ __forceinline__ int scal_slots(int step)
+constexpr int scal_slots(int step)
 {
     switch (step) {
     case SC_ALPHA: return 0x03;     // <r0, v>
@@ -425,51 +426,72 @@ __device__ __forceinline__ int scal_slots(int step)
     }
 }
 
+// Bound by the latency of its loads: the state is fetched beside the
+// partial sums, the loads of up to 1024 site blocks are issued before the
+// first is added, and the tree takes one barrier (four threads' sums per
+// lane, then shuffles) -- the same order of additions as a halving tree over
+// 256 threads.  8.5 -> 4.8 us a launch with 1024 site blocks and 12 systems,
+// 4.5 -> 2.6 us with 64 site blocks and one.
+template <int STEP>
 __global__ __launch_bounds__(256) void k_scal(ScalArgs a)
 {
     const int sys = blockIdx.x;
-    if (a.mask) {
-        if (!a.mask[sys]) return;
-    } else if (!a.active[sys]) {
-        return;
-    }
+    const int act0 = a.active[sys];
+    if (a.mask ? !a.mask[sys] : !act0) return;
     int l = 0;
     for (int k = 1; k < FL_MAXLAT; ++k)
         if (k < a.B.nlat && sys >= a.B.lat[k].sys0) l = k;
     const int nsb = a.B.lat[l].nsb, nb = a.B.nsb_max;
+    constexpr int used = scal_slots(STEP);  // only the slots this step reads
     __shared__ double red[6][256];
     __shared__ SysState snew;
-    // only the slots this step reads (the same for the whole block)
-    const int used = scal_slots(a.step);
-    for (int slot = 0; slot < 6; ++slot) {
-        if (!((used >> slot) & 1)) continue;
-        double acc = 0;
-        for (int sb = threadIdx.x; sb < nsb; sb += 256) acc += a.partial[pidx(slot, a.nsys, sys, nb, sb)];
-        red[slot][threadIdx.x] = acc;
+    constexpr int NW = (int)(sizeof(SysState) / 8);
+    static_assert(sizeof(SysState) % 8 == 0, "SysState is written in 8-byte words");
+    // the old state waits in the shared copy
+    if ((int)threadIdx.x < NW)
+        ((unsigned long long *)&snew)[threadIdx.x] = ((const unsigned long long *)(a.st + sys))[threadIdx.x];
+    double acc[6];
+#pragma unroll
+    for (int slot = 0; slot < 6; ++slot) acc[slot] = 0.0;
+    for (int sb = threadIdx.x; sb < nsb; sb += 1024) {
+        double v[6][4];
+#pragma unroll
+        for (int slot = 0; slot < 6; ++slot)
+            if ((used >> slot) & 1)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int q = min(sb + 256 * k, nsb - 1);
+                    v[slot][k] = a.partial[pidx(slot, a.nsys, sys, nb, q)];
+                }
+#pragma unroll
+        for (int slot = 0; slot < 6; ++slot)
+            if ((used >> slot) & 1)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc[slot] += sb + 256 * k < nsb ? v[slot][k] : 0.0;
     }
+#pragma unroll
+    for (int slot = 0; slot < 6; ++slot)
+        if ((used >> slot) & 1) red[slot][threadIdx.x] = acc[slot];
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int slot = 0; slot < 6; ++slot)
-                if ((used >> slot) & 1) red[slot][threadIdx.x] += red[slot][threadIdx.x + w];
-        __syncthreads();
-    }
     if (threadIdx.x >= FL_WAVE) return;
+    double P[6];
+#pragma unroll
+    for (int slot = 0; slot < 6; ++slot) {
+        P[slot] = 0.0;
+        if (!((used >> slot) & 1)) continue;
+        const double *q = red[slot] + threadIdx.x;
+        P[slot] = wave_sum((q[0] + q[128]) + (q[64] + q[192]));
+    }
     if (threadIdx.x == 0) {
-        double P[6];
-        for (int slot = 0; slot < 6; ++slot) P[slot] = ((used >> slot) & 1) ? red[slot][0] : 0.0;
-        SysState s = a.st[sys];
-        const int act0 = a.active[sys];
+        SysState s = snew;
         int act = act0;
-        scal_step(a, P, s, act);
+        scal_step<STEP>(a, P, s, act);
         snew = s;
         if (act != act0) a.active[sys] = act;
     }
     // the flag store completes before the state is written as one store
     // instruction of 8-byte words, one per lane, which ends the kernel
     store_drain();
-    constexpr int NW = (int)(sizeof(SysState) / 8);
-    static_assert(sizeof(SysState) % 8 == 0, "SysState is written in 8-byte words");
     if ((int)threadIdx.x < NW)
         ((unsigned long long *)(a.st + sys))[threadIdx.x] = ((const unsigned long long *)&snew)[threadIdx.x];
 }
@@ -491,9 +513,17 @@ void launch_blas(VecFormat vf, const BlasArgs &a, hipStream_t s)
 void launch_scalars(const ScalArgs &a, hipStream_t s)
 {
     if (a.nsys == 0) return;
-    if (a.step < SC_ALPHA || a.step > SC_CG_REZ) {
-        launch_unsupported("scalar step");
-        return;
+    const dim3 grid(a.nsys), block(256);
+    switch (a.step) {
+    case SC_ALPHA: hipLaunchKernelGGL(k_scal<SC_ALPHA>, grid, block, 0, s, a); break;
+    case SC_OMEGA: hipLaunchKernelGGL(k_scal<SC_OMEGA>, grid, block, 0, s, a); break;
+    case SC_BETA: hipLaunchKernelGGL(k_scal<SC_BETA>, grid, block, 0, s, a); break;
+    case SC_RESET: hipLaunchKernelGGL(k_scal<SC_RESET>, grid, block, 0, s, a); break;
+    case SC_INIT: hipLaunchKernelGGL(k_scal<SC_INIT>, grid, block, 0, s, a); break;
+    case SC_CG_INIT: hipLaunchKernelGGL(k_scal<SC_CG_INIT>, grid, block, 0, s, a); break;
+    case SC_CG_ALPHA: hipLaunchKernelGGL(k_scal<SC_CG_ALPHA>, grid, block, 0, s, a); break;
+    case SC_CG_BETA: hipLaunchKernelGGL(k_scal<SC_CG_BETA>, grid, block, 0, s, a); break;
+    case SC_CG_REZ: hipLaunchKernelGGL(k_scal<SC_CG_REZ>, grid, block, 0, s, a); break;
+    default: launch_unsupported("scalar step"); break;
     }
-    hipLaunchKernelGGL(k_scal, dim3(a.nsys), dim3(256), 0, s, a);
 }
