@@ -158,6 +158,15 @@ __device__ __forceinline__ void buf_st8(const Buf &b, v2f v, int voff, int soff)
     __builtin_amdgcn_raw_buffer_store_b64(v, b.r, voff, soff, 0);
 }
 
+// workgroup barrier for LDS traffic alone: loads and stores of device memory
+// stay in flight across it (__syncthreads waits for them as well)
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // N 16-byte vectors of one lane at byte offsets voff + c * cstride (cstride
 // wave-uniform), as one store group
 template <int N, int CP = 0>
@@ -793,21 +802,37 @@ struct LinkQ16R12 {
     // in words 2e, 2e + 1 of entry e = 3a + b of the matrix applied
     static constexpr float HALF_UNIT = 2.0f / 32767.0f;
     static constexpr int PK_SNC = 18;
+    // All in integers: rows 0 and 1 halved with rounding, row 2 (the conjugate
+    // cross product) from exact int16 products summed in int32 (below 2^30:
+    // each entry of a unit matrix times 32767^2), rounded once to half scale;
+    // about 75 vector instructions a link where the decode to FP32, the FP32
+    // cross product and the re-encoding took 130
     template <bool ADJ>
     __device__ static __forceinline__ void stage_pk(const V v[NC], SV w[PK_SNC])
     {
-        cx<float> U[3][3];
-        unpack(v, U);
-        const float k = 0.5f * UNIT;
+        const s2 r[6] = {as_s2(v[0].x), as_s2(v[0].y), as_s2(v[1].x), as_s2(v[1].y), as_s2(v[2].x), as_s2(v[2].y)};
+        s2 u[9];
+#pragma unroll
+        for (int e = 0; e < 6; ++e) u[e] = __builtin_elementwise_add_sat(r[e], (s2){1, 1}) >> 1;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            // conj(x y - z q), x, z of row 0 and y, q of row 1
+            const s2 x = r[(b + 1) % 3], z = r[(b + 2) % 3], y = r[3 + (b + 2) % 3], q = r[3 + (b + 1) % 3];
+            int re = sdot2_first(x, y * (s2){1, -1});
+            re = __builtin_amdgcn_sdot2(z, q * (s2){-1, 1}, re, false);
+            int im = sdot2_first(z, swp(q));
+            im = __builtin_amdgcn_sdot2(x, swp(y) * (s2){-1, -1}, im, false);
+            constexpr float k = 0.5f * UNIT * UNIT;
+            u[6 + b] = as_s2(h16_pack((float)re * k, (float)im * k));
+        }
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                const cx<float> u = ADJ ? U[b][a] : U[a][b];
-                const float ur = u.re * k, ui = u.im * k;
                 const int e = 3 * a + b;
-                w[2 * e] = ADJ ? h16_pack(ur, ui) : h16_pack(ur, -ui);
-                w[2 * e + 1] = ADJ ? h16_pack(-ui, ur) : h16_pack(ui, ur);
+                const s2 t = ADJ ? u[3 * b + a] : u[e];
+                w[2 * e] = __builtin_bit_cast(unsigned, ADJ ? t : t * (s2){1, -1});
+                w[2 * e + 1] = __builtin_bit_cast(unsigned, ADJ ? swp(t) * (s2){-1, 1} : swp(t));
             }
     }
 };

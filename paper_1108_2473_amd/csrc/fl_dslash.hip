@@ -263,12 +263,10 @@ struct LdsSrc {
     }
 };
 
-// Source of the packed integer hop (16-bit fields, lds modes 3 and 4): x/y
-// neighbours from the wave's LDS window (mode 3) or from memory like the
-// z/t neighbours (mode 4), links from the workgroup's half-scale staging.
-// The factor returned with a site's integers is its scale times the staged
-// link unit.
-template <bool WIN>
+// Source of the packed integer hop with windows (16-bit fields, lds mode 3):
+// x/y neighbours from the wave's LDS window, links from the workgroup's
+// half-scale staging.  The factor returned with a site's integers is its
+// scale times the staged link unit.
 struct LdsSrcQ16 {
     static constexpr bool PACKED_I16 = true;
     Buf in;
@@ -279,7 +277,7 @@ struct LdsSrcQ16 {
     __device__ __forceinline__ float spinor_i16(int i, s2 p[12]) const
     {
         constexpr float k = LinkQ16R12::HALF_UNIT;
-        if (WIN && MU < 2)
+        if (MU < 2)
             return k * SpinorFmt<H16>::lds_load_i16(win, wsmax, i - wlo, p);
         else
             return k * SpinorFmt<H16>::load_i16(in, Vh, i, p);
@@ -291,33 +289,121 @@ struct LdsSrcQ16 {
     }
 };
 
-// checkerboard index of the backward neighbour x - mu of site (p, i)
-__device__ __forceinline__ int back_neighbour(const LatGeom &g, const Coord &c, int mu)
-{
-    const int Lh0 = g.Lh0, Ly = g.L[1], Lz = g.L[2], Lt = g.L[3], xh = c.x >> 1;
-    if (mu == 0) {
-        int xb = (c.x == 0) ? g.L[0] - 1 : c.x - 1;
-        return (xb >> 1) + Lh0 * c.rest;
-    } else if (mu == 1) {
-        int yb = (c.y == 0) ? Ly - 1 : c.y - 1;
-        return xh + Lh0 * (yb + Ly * (c.z + Lz * c.t));
-    } else if (mu == 2) {
-        int zb = (c.z == 0) ? Lz - 1 : c.z - 1;
-        return xh + Lh0 * (c.y + Ly * (zb + Lz * c.t));
+// Source of the packed integer hop without windows (lds mode 4): all
+// neighbours from memory, links from the workgroup's staging, 16 bytes a read
+struct MemSrcQ16 {
+    Buf in;
+    int Vh, lane;
+    const unsigned char *lk;
+    template <int MU>
+    __device__ __forceinline__ float spinor_i16(int i, s2 p[12]) const
+    {
+        return LinkQ16R12::HALF_UNIT * SpinorFmt<H16>::load_i16(in, Vh, i, p);
     }
-    int tb = (c.t == 0) ? Lt - 1 : c.t - 1;
-    return xh + Lh0 * (c.y + Ly * (c.z + Lz * tb));
+    // LDS: [slot][16-byte vectors 0-3, then the last 8 bytes][lane]
+    static constexpr int SLOT_BYTES = 72 * FL_WAVE;
+    __device__ __forceinline__ void link_i16(int dslot, unsigned L[18]) const
+    {
+        const unsigned char *b = lk + dslot * SLOT_BYTES;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const v4u v = ((const v4u *)(b + c * 16 * FL_WAVE))[lane];
+            L[4 * c] = v.x;
+            L[4 * c + 1] = v.y;
+            L[4 * c + 2] = v.z;
+            L[4 * c + 3] = v.w;
+        }
+        const v2u v = ((const v2u *)(b + 64 * FL_WAVE))[lane];
+        L[16] = v.x;
+        L[17] = v.y;
+    }
+    __device__ static __forceinline__ void put(unsigned char *lk, int dslot, int lane, const unsigned w[18])
+    {
+        unsigned char *b = lk + dslot * SLOT_BYTES;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            ((v4u *)(b + c * 16 * FL_WAVE))[lane] = v4u{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]};
+        ((v2u *)(b + 64 * FL_WAVE))[lane] = v2u{w[16], w[17]};
+    }
+};
+
+// The packed integer hop of 16-bit fields without windows (lds mode 4, the
+// built-in choice).  With a full chip it is held between vector issue (55-70 %
+// of the cycles) and the traffic behind L2, neither alone: at 16^3x32 with 384
+// right-hand sides 831 us a launch, with the link staging decoded to FP32
+// instead of done in integers 837; with few right-hand sides the staging is
+// on the critical path (one: 8.0 against 10.7 us; 7 of 10x6x14x18: 6.9
+// against 7.4).  Issuing the first neighbour loads before the barrier: 3-8 %
+// faster below 100 MB of input, 5-7 % slower above (L2 holds less of what
+// neighbouring blocks read again); both by a run-time switch: no gain left.
+template <bool DAG, int EPI>
+__global__ __launch_bounds__(1024) void k_dslash_q16(DslashArgs a)
+{
+    extern __shared__ unsigned char smem[];
+    TileInfo T = tile_info(a.B);
+    const LatGeom &g = a.B.lat[T.lat];
+    const int Vh = g.Vh;
+    const int lane = threadIdx.x % FL_WAVE;
+    const bool live = T.valid_rhs && !(a.mask && !a.mask[T.sys]);
+    const int rhs = __builtin_amdgcn_readfirstlane(T.valid_rhs ? T.rhs : 0);
+    // lanes past the lattice's end take its last site
+    const int site = T.valid_site ? T.site : Vh - 1;
+    const Coord c = cb_coords(g, a.par, site);
+    int nb[8];
+    neighbours(g, c, site, nb);
+    constexpr int PF = 2;  // neighbour loads two directions ahead
+    MemSrcQ16 src;
+    src.in = spinor_buf<H16>(a.in[T.lat], Vh, rhs);
+    src.Vh = Vh;
+    src.lane = lane;
+    src.lk = smem;
+    {
+        // the 8 links (4 forward at the site, 4 backward at the neighbour) of
+        // the block's 64 sites, shared by all its right-hand sides
+        typedef LinkQ16R12 LK;
+        const Buf gbuf = make_buf(a.gauge[T.lat], 8u * LK::BYTES * (unsigned)Vh);
+        const int nw = blockDim.x / FL_WAVE;
+        LK::V v[LK::NC];
+        auto fetch = [&](int d) {
+            const int mu = d >> 1, adj = d & 1;
+            const int idx = adj ? (mu == 0 ? nb[1] : (mu == 1 ? nb[3] : (mu == 2 ? nb[5] : nb[7]))) : site;
+#pragma unroll
+            for (int k = 0; k < LK::NC; ++k)
+                v[k] = LK::buf_get(gbuf, idx * LK::ESZ, ((mu * 2 + (adj ? 1 - a.par : a.par)) * LK::NC + k) * Vh * LK::ESZ);
+        };
+        int d = __builtin_amdgcn_readfirstlane(threadIdx.x / FL_WAVE);
+        if (d < 8) fetch(d);
+        for (; d < 8; d += nw) {
+            unsigned w[LK::PK_SNC];
+            if (d & 1)
+                LK::stage_pk<true>(v, w);
+            else
+                LK::stage_pk<false>(v, w);
+            MemSrcQ16::put(smem, d, lane, w);
+            if (d + nw < 8) fetch(d + nw);
+        }
+    }
+    lds_barrier();
+    if (!live) return;
+    float q0 = 0, q1 = 0, q2 = 0;
+    if (T.valid_site) {
+        cx<float> acc[12];
+        hop_site_pk<DAG, PF>(g, c, nb, src, acc);
+        epilogue<H16, EPI>(a, T, g, rhs, acc, q0, q1, q2);
+    }
+    reduce_partials<EPI>(a, T, q0, q1, q2);
 }
 
 // SLINK: links staged in LDS; PK (16-bit fields only, with SLINK): the
 // packed integer hop with half-scale staged links;
 // NOWIN: no neighbour windows (x/y neighbours from memory like z/t); with
-// SLINK and without PK the LDS holds the staged links only, so that more
-// workgroups fit a CU than with the windows
+// SLINK the LDS holds the staged links only, so that more workgroups fit a CU
+// than with the windows
 template <typename S, class LK, bool DAG, int EPI, bool SLINK, bool PK = false, bool NOWIN = false>
 __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024) void k_dslash_lds(DslashArgs a)
 {
-    static_assert(!PK || (SLINK && std::is_same<LK, LinkQ16R12>::value), "packed hop needs staged Q16 links");
+    static_assert(!PK || (SLINK && !NOWIN && std::is_same<LK, LinkQ16R12>::value),
+                  "packed hop with windows needs staged Q16 links");
     typedef typename SpinorFmt<S>::R R;
     typedef typename LK::V LV;
     typedef typename LK::SV LSV;
@@ -340,19 +426,22 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
     const int rhs = __builtin_amdgcn_readfirstlane(T.valid_rhs ? T.rhs : 0);
     const Buf gbuf = make_buf(a.gauge[T.lat], (unsigned)(8u * LK::NC * LK::ESZ * (unsigned)Vh));
     Buf ibuf = spinor_buf<S>(a.in[T.lat], Vh, rhs);
+    const Coord c = cb_coords(g, a.par, T.valid_site ? T.site : Vh - 1);
+    int nb[8];
+    neighbours(g, c, T.valid_site ? T.site : Vh - 1, nb);
     if (SLINK) {
         // the 8 links (4 forward at the site, 4 backward at the neighbour) of
         // the block's 64 sites, shared by all its right-hand sides
         for (int k = threadIdx.x; k < 8 * FL_WAVE; k += blockDim.x) {
             // one direction slot per wave (64 consecutive k)
+            // (s is this lane, so the site and its neighbours are the lane's own)
             const int dslot = __builtin_amdgcn_readfirstlane(k / FL_WAVE), s = k % FL_WAVE, mu = dslot >> 1;
             const int site = i0 + s;
             LV v[LK::NC];
             if (site < Vh) {
                 int idx = site, par = a.par;
                 if (dslot & 1) {
-                    Coord c = cb_coords(g, a.par, site);
-                    idx = back_neighbour(g, c, mu);
+                    idx = mu == 0 ? nb[1] : (mu == 1 ? nb[3] : (mu == 2 ? nb[5] : nb[7]));
                     par = 1 - a.par;
                 }
 #pragma unroll
@@ -386,10 +475,9 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
     if (!live) return;
     R q0 = 0, q1 = 0, q2 = 0;
     if (T.valid_site) {
-        Coord c = cb_coords(g, a.par, T.site);
         cx<R> acc[12];
         if constexpr (PK) {
-            LdsSrcQ16<!NOWIN> src;
+            LdsSrcQ16 src;
             src.in = ibuf;
             src.Vh = Vh;
             src.wlo = wlo;
@@ -397,10 +485,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             src.lane = lane;
             src.win = win;
             src.lk = (const unsigned *)lk;
-            if constexpr (NOWIN)
-                hop_site_pk<DAG, 2>(g, c, src, acc);  // neighbour loads two directions ahead
-            else
-                hop_site<DAG, R>(g, a.par, T.site, c, src, acc);
+            hop_site<DAG, R>(g, a.par, T.site, c, nb, src, acc);
         } else {
             LdsSrc<S, LK, SLINK, !NOWIN> src;
             src.in = ibuf;
@@ -413,7 +498,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             src.lane = lane;
             src.win = win;
             src.lk = lk;
-            hop_site<DAG, R>(g, a.par, T.site, c, src, acc);
+            hop_site<DAG, R>(g, a.par, T.site, c, nb, src, acc);
         }
         epilogue<S, EPI>(a, T, g, rhs, acc, q0, q1, q2);
     }
@@ -426,10 +511,11 @@ size_t dslash_lds_bytes_t(int RT, int wsmax, int lds)
     // modes: 1 windows, 2 windows + staged links, 3 (16-bit) windows + packed
     // staged links, 4 staged links only (packed for 16-bit fields)
     constexpr bool Q16 = std::is_same<LK, LinkQ16R12>::value;
+    if (Q16 && lds == 4) return 8 * MemSrcQ16::SLOT_BYTES;
     size_t b = lds == 4 ? 0 : (size_t)RT * SpinorFmt<S>::SITE_BYTES * wsmax;
-    if (lds == 2 || (lds == 4 && !Q16)) b += (size_t)8 * LK::SNC * FL_WAVE * sizeof(typename LK::SV);
+    if (lds == 2 || lds == 4) b += (size_t)8 * LK::SNC * FL_WAVE * sizeof(typename LK::SV);
     if constexpr (Q16)
-        if (lds >= 3) b += (size_t)8 * LK::PK_SNC * FL_WAVE * sizeof(typename LK::SV);
+        if (lds == 3) b += (size_t)8 * LK::PK_SNC * FL_WAVE * sizeof(typename LK::SV);
     return b;
 }
 
@@ -448,7 +534,7 @@ void launch_one(const DslashArgs &a, dim3 grid, dim3 block, hipStream_t s)
                 return;
             }
             if (a.lds == 4) {
-                hipLaunchKernelGGL((k_dslash_lds<S, LK, DAG, EPI, true, true, true>), grid, block, shm, s, a);
+                hipLaunchKernelGGL((k_dslash_q16<DAG, EPI>), grid, block, shm, s, a);
                 return;
             }
         } else if (a.lds == 4) {

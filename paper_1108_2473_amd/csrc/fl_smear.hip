@@ -165,15 +165,6 @@ __device__ __forceinline__ void plane_load(const Buf &b, int voff, int soff, int
     }
 }
 
-// workgroup barrier for LDS traffic alone: loads and stores of device memory
-// stay in flight across it (__syncthreads waits for them as well)
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __global__ __launch_bounds__(PL_T, 2) void k_smear_plane(PlaneArgs a)
 {
     extern __shared__ double2 lds[];  // [2][slot][psi, U_x^+ psi, U_y^+ psi of one spin component]

@@ -256,41 +256,45 @@ __device__ __forceinline__ void hop_dir(int p, int i, int nf, int nb, R sf, R sb
     }
 }
 
+// checkerboard indices of the eight neighbours of site i at c, slot 2 mu + 0
+// forward / 1 backward: offsets of wave-uniform strides, no multiplication
+// per lane (a 32-bit product issues at a quarter of the rate)
+__device__ __forceinline__ void neighbours(const LatGeom &g, const Coord &c, int i, int nb[8])
+{
+    const int Lh0 = g.Lh0, s2 = Lh0 * g.L[1], s3 = s2 * g.L[2], s4 = s3 * g.L[3];
+    const int xh = c.x >> 1, xo = c.x & 1;
+    nb[0] = i + (xo ? (xh + 1 == Lh0 ? 1 - Lh0 : 1) : 0);
+    nb[1] = i + (xo ? 0 : (xh == 0 ? Lh0 - 1 : -1));
+    nb[2] = i + (c.y + 1 == g.L[1] ? Lh0 - s2 : Lh0);
+    nb[3] = i + (c.y == 0 ? s2 - Lh0 : -Lh0);
+    nb[4] = i + (c.z + 1 == g.L[2] ? s2 - s3 : s2);
+    nb[5] = i + (c.z == 0 ? s3 - s2 : -s2);
+    nb[6] = i + (c.t + 1 == g.L[3] ? s3 - s4 : s3);
+    nb[7] = i + (c.t == 0 ? s4 - s3 : -s3);
+}
+
+// the sum over the eight hops into site i, neighbour indices given; the time
+// hops that wrap carry the boundary factor
+template <bool DAG, typename R, class SRC>
+__device__ __forceinline__ void hop_site(const LatGeom &g, int p, int i, const Coord &c, const int nb[8],
+                                         const SRC &src, cx<R> acc[12])
+{
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[k] = cx<R>{(R)0, (R)0};
+    hop_dir<0, DAG, R>(p, i, nb[0], nb[1], (R)1, (R)1, src, acc);
+    hop_dir<1, DAG, R>(p, i, nb[2], nb[3], (R)1, (R)1, src, acc);
+    hop_dir<2, DAG, R>(p, i, nb[4], nb[5], (R)1, (R)1, src, acc);
+    hop_dir<3, DAG, R>(p, i, nb[6], nb[7], c.t + 1 == g.L[3] ? (R)g.bc_t : (R)1, c.t == 0 ? (R)g.bc_t : (R)1, src,
+                       acc);
+}
+
 template <bool DAG, typename R, class SRC>
 __device__ __forceinline__ void hop_site(const LatGeom &g, int p, int i, const Coord &c, const SRC &src,
                                          cx<R> acc[12])
 {
-#pragma unroll
-    for (int k = 0; k < 12; ++k) acc[k] = cx<R>{(R)0, (R)0};
-    const int Lh0 = g.Lh0, xh = c.x >> 1;
-    {   // x
-        int xf = (c.x + 1 == g.L[0]) ? 0 : c.x + 1;
-        int xb = (c.x == 0) ? g.L[0] - 1 : c.x - 1;
-        hop_dir<0, DAG, R>(p, i, (xf >> 1) + Lh0 * c.rest, (xb >> 1) + Lh0 * c.rest, (R)1, (R)1, src, acc);
-    }
-    const int Ly = g.L[1], Lz = g.L[2], Lt = g.L[3];
-    {   // y
-        int yf = (c.y + 1 == Ly) ? 0 : c.y + 1;
-        int yb = (c.y == 0) ? Ly - 1 : c.y - 1;
-        int zt = Ly * (c.z + Lz * c.t);
-        hop_dir<1, DAG, R>(p, i, xh + Lh0 * (yf + zt), xh + Lh0 * (yb + zt), (R)1, (R)1, src, acc);
-    }
-    {   // z
-        int zf = (c.z + 1 == Lz) ? 0 : c.z + 1;
-        int zb = (c.z == 0) ? Lz - 1 : c.z - 1;
-        int base = xh + Lh0 * c.y;
-        int s = Lh0 * Ly;
-        hop_dir<2, DAG, R>(p, i, base + s * (zf + Lz * c.t), base + s * (zb + Lz * c.t), (R)1, (R)1, src, acc);
-    }
-    {   // t, with the boundary factor on the hops that wrap
-        int tf = c.t + 1, tb = c.t - 1;
-        R sf = (R)1, sb = (R)1;
-        if (tf == Lt) { tf = 0; sf = (R)g.bc_t; }
-        if (tb < 0) { tb = Lt - 1; sb = (R)g.bc_t; }
-        int base = xh + Lh0 * (c.y + Ly * c.z);
-        int s = Lh0 * Ly * Lz;
-        hop_dir<3, DAG, R>(p, i, base + s * tf, base + s * tb, sf, sb, src, acc);
-    }
+    int nb[8];
+    neighbours(g, c, i, nb);
+    hop_site<DAG, R>(g, p, i, c, nb, src, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -327,38 +331,12 @@ __device__ __forceinline__ void pk_step(const SRC &src, const int nb[8], const f
 }
 
 template <bool DAG, int PF, class SRC>
-__device__ __forceinline__ void hop_site_pk(const LatGeom &g, const Coord &c, const SRC &src, cx<float> acc[12])
+__device__ __forceinline__ void hop_site_pk(const LatGeom &g, const Coord &c, const int nb[8], const SRC &src,
+                                            cx<float> acc[12])
 {
-    int nb[8];
     float bf[8];
-    const int Lh0 = g.Lh0, Ly = g.L[1], Lz = g.L[2], Lt = g.L[3], xh = c.x >> 1;
-    {
-        const int xf = (c.x + 1 == g.L[0]) ? 0 : c.x + 1, xb = (c.x == 0) ? g.L[0] - 1 : c.x - 1;
-        nb[0] = (xf >> 1) + Lh0 * c.rest;
-        nb[1] = (xb >> 1) + Lh0 * c.rest;
-    }
-    {
-        const int yf = (c.y + 1 == Ly) ? 0 : c.y + 1, yb = (c.y == 0) ? Ly - 1 : c.y - 1;
-        const int zt = Ly * (c.z + Lz * c.t);
-        nb[2] = xh + Lh0 * (yf + zt);
-        nb[3] = xh + Lh0 * (yb + zt);
-    }
-    {
-        const int zf = (c.z + 1 == Lz) ? 0 : c.z + 1, zb = (c.z == 0) ? Lz - 1 : c.z - 1;
-        const int base = xh + Lh0 * c.y, s = Lh0 * Ly;
-        nb[4] = base + s * (zf + Lz * c.t);
-        nb[5] = base + s * (zb + Lz * c.t);
-    }
-    {
-        int tf = c.t + 1, tb = c.t - 1;
-        bf[6] = 1.0f;
-        bf[7] = 1.0f;
-        if (tf == Lt) { tf = 0; bf[6] = (float)g.bc_t; }
-        if (tb < 0) { tb = Lt - 1; bf[7] = (float)g.bc_t; }
-        const int base = xh + Lh0 * (c.y + Ly * c.z), s = Lh0 * Ly * Lz;
-        nb[6] = base + s * tf;
-        nb[7] = base + s * tb;
-    }
+    bf[6] = c.t + 1 == g.L[3] ? (float)g.bc_t : 1.0f;
+    bf[7] = c.t == 0 ? (float)g.bc_t : 1.0f;
 #pragma unroll
     for (int d = 0; d < 6; ++d) bf[d] = 1.0f;
 #pragma unroll
