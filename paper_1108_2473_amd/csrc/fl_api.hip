@@ -401,6 +401,26 @@ void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G)
     int cap = 1;
     while (cap < nrhs && cap < maxrt) cap *= 2;
     *RT = std::max(1, std::min(std::min(rt, maxrt), cap));
+    if (c->tune_rt[fmt] <= 0 && nrhs > 8) {
+        // a last block of few right-hand sides leaves waves of its workgroups
+        // idle (12 in blocks of 8: 4 of 16): smaller workgroups where their
+        // number times a workgroup's time is less.  Times in per cent of an
+        // 8-wave workgroup's, measured on the hop at 16^3x32: 4 waves 57
+        // (16-bit), 60 (FP32), 50 (FP64), 6 waves 80 (FP32) and 77 (FP64; 97
+        // for 16-bit).  12 right-hand sides: 16-bit 35.0 us in blocks of 8,
+        // 30.4 of 4; FP32 59.3, 49.4 of 6; FP64 148, 124 of 4
+        const int six = fmt == LINK_Q16_R12 ? 97 : (fmt == LINK_F64_R18 ? 77 : 80);
+        const int four = fmt == LINK_Q16_R12 ? 57 : (fmt == LINK_F64_R18 ? 50 : 60);
+        int best = 100 * ((nrhs + 7) / 8);
+        const int shape[2][2] = {{6, six}, {4, four}};
+        for (const auto &q : shape) {
+            const int t = q[1] * ((nrhs + q[0] - 1) / q[0]);
+            if (t < best) {
+                best = t;
+                *RT = q[0];
+            }
+        }
+    }
     *G = c->tune_g[fmt] > 0 ? c->tune_g[fmt] : 1;
 }
 
