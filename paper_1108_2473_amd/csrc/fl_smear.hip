@@ -576,8 +576,7 @@ fl_status fl_pion_corr(fl_ctx *c, long long y0, const fl_solver_params *p, doubl
     double *src = (double *)ws_get(c, WS_PI_SRC, 12 * per), *sol = (double *)ws_get(c, WS_PI_SOL, 12 * per);
     double2 *rho = (double2 *)ws_get(c, WS_PI_RHO, (size_t)V * sizeof(double2));
     double2 *P = (double2 *)ws_get(c, WS_CORR_OUT, (size_t)nmom * T * sizeof(double2));
-    int *dmom = (int *)ws_get(c, WS_CORR_IDX, sizeof(int) * 3 * (size_t)nmom);
-    if (!src || !sol || !rho || !P || !dmom) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
+    if (!src || !sol || !rho || !P) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
     fl_status e;
     // the 12 spin-colour point sources at y0 (canonical layout: spin, colour, re/im)
     if ((e = hip_check(c, hipMemsetAsync(src, 0, 12 * per, c->stream), "clear sources"))) return e;
@@ -590,10 +589,7 @@ fl_status fl_pion_corr(fl_ctx *c, long long y0, const fl_solver_params *p, doubl
     if (se != FL_OK && se != FL_ERR_NOCONV && se != FL_ERR_BREAKDOWN) return se;
     if (smear_sink && n > 0 && (e = smear_canon(c, sol, 12, alpha, n, norm))) return e;
     hipLaunchKernelGGL(k_density, dim3(blocks(V)), dim3(BLK), 0, c->stream, sol, rho, V, 12);
-    if ((e = hip_check(c, hipMemcpyAsync(dmom, mom, sizeof(int) * 3 * (size_t)nmom, hipMemcpyHostToDevice,
-                                         c->stream), "upload momenta")))
-        return e;
-    launch_momproj(rho, P, dmom, 1, T, nmom, c->L, c->stream);
+    launch_momproj(rho, P, mom, 1, T, nmom, c->L, c->stream);
     std::vector<double> hp((size_t)nmom * T * 2), out((size_t)nmom * T * 2);
     if ((e = hip_check(c, hipMemcpyAsync(hp.data(), P, hp.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream),
                        "download")) ||

@@ -58,6 +58,25 @@ def test_projection_gamma_counts(F, ng):
     lat.close()
 
 
+@pytest.mark.parametrize("dims,nmom", [((18, 16, 4, 2), 3), ((2, 2, 4, 2), 5), ((6, 10, 2, 4), 65), ((16, 16, 2, 2), 131)])
+def test_projection_planes_and_many_momenta(F, dims, nmom):
+    """Planes larger than a workgroup, of one site per thread, dividing it and
+    not; more momenta and pairs than one launch takes; integer momenta beyond
+    the lattice's extents on either side."""
+    Vs, T = dims[0] * dims[1] * dims[2], dims[3]
+    mom = [((7 * k) % 41 - 20, (5 * k) % 37 - 18, (3 * k) % 31 - 15) for k in range(nmom)]
+    lat = F.Lattice(dims, -1)
+    L = _rand((2, T, Vs), 15)
+    P = lat.momentum_project(L, mom)
+    W = O.momentum_project(L, dims, mom)
+    assert np.abs(P - W).max() <= 1e-12 * np.sqrt(Vs)
+    pairs = [(k % 2, (k // 2) % 2) for k in range(nmom)]
+    D = lat.disconnected_corr(P, P, pairs)
+    Dw = O.disconnected_correlator(W, W, Vs, pairs)
+    assert np.abs(D - Dw).max() <= 1e-12 * np.abs(Dw).max()
+    lat.close()
+
+
 def test_device_arrays_and_argument_checks(F):
     import torch
     dims = (4, 4, 4, 8)
