@@ -11,7 +11,7 @@
 #include "fl_host.h"
 
 void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *in, void *out, const void *x,
-                  double ca, double cb, bool dag, int epi)
+                  double ca, double cb, bool dag, int epi, bool split_ok)
 {
     int RT, G;
     tile_shape(c, LINK_F64_R18, nrhs, &RT, &G);
@@ -29,7 +29,7 @@ void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *i
     a.ca[0] = ca;
     a.cb[0] = cb;
     if (epi < 0) epi = x ? EPI_XPAY : EPI_PLAIN;
-    dslash_config(c, LINK_F64_R18, a);
+    dslash_config(c, LINK_F64_R18, a, split_ok);
     launch_dslash(LINK_F64_R18, a, dag, epi, c->stream);
 }
 
@@ -138,9 +138,9 @@ fl_status check_params(fl_ctx *c, const fl_solver_params *p)
 
 // single-lattice hopping launch on FP64 fields
 void hop64(fl_ctx *c, int nrhs, int par, const void *in, void *out, const void *x, double ca, double cb, bool dag,
-           int epi = -1)
+           bool same_bits = false)
 {
-    hop64_launch(c, links(c, LINK_F64_R18), nrhs, par, in, out, x, ca, cb, dag, epi);
+    hop64_launch(c, links(c, LINK_F64_R18), nrhs, par, in, out, x, ca, cb, dag, -1, !same_bits);
 }
 
 // |f|^2 per right-hand side of FP64 (even, odd) fields, summed on the host in
@@ -388,6 +388,13 @@ BatchGeom batch_geom(fl_ctx *const *ctx, const int *nrhs, int nlat, int RT, int 
     return B;
 }
 
+// Largest number of 64-site tiles for which the hop runs a wave per direction.
+// Whole solves, before -> after: FP64 8^3x16, 64 tiles, 1.84 -> 1.72 ms, 324
+// tiles 3.06 -> 2.78, 768 tiles 3.03 -> 3.60 (links read once per right-hand
+// side, and waves enough without it); 16-bit 64 tiles 4.69 -> 3.51, 1024 tiles
+// 6.23 -> 5.46; FP32 64 tiles 1.96 -> 1.63, 1024 tiles 3.88 -> 2.78
+static int split_tiles(LinkFormat fmt) { return fmt == LINK_F64_R18 ? 330 : 1024; }
+
 void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G)
 {
     const int maxrt = fmt == LINK_F64_R18 ? 8 : 16;
@@ -424,8 +431,32 @@ void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G)
     *G = c->tune_g[fmt] > 0 ? c->tune_g[fmt] : 1;
 }
 
-void dslash_config(const fl_ctx *c, LinkFormat fmt, DslashArgs &a)
+void dslash_config(const fl_ctx *c, LinkFormat fmt, DslashArgs &a, bool split_ok)
 {
+    if (split_ok && c->tune_lds[fmt] < 0 && c->tune_rt[fmt] <= 0 && fmt != LINK_BF16_R12) {
+        int tiles = 0, few = 1;
+        for (int l = 0; l < a.B.nlat; ++l) {
+            tiles += a.B.lat[l].nsb * a.B.lat[l].nrhs;
+            few &= a.B.lat[l].nrhs < 4;
+        }
+        // the FP64 and FP32 results round differently from the other kernels'
+        // (which FP64 workgroups of fewer than 4 right-hand sides do in any case)
+        if (tiles <= split_tiles(fmt) && (few || fmt == LINK_Q16_R12)) {
+            // a workgroup per 64 sites of one right-hand side
+            a.lds = 5;
+            a.wsmax = 0;
+            int t0 = 0;
+            for (int l = 0; l < a.B.nlat; ++l) {
+                LatGeom &g = a.B.lat[l];
+                g.nrb = g.nrhs;
+                g.tile0 = t0;
+                t0 += g.nsb * g.nrb;
+            }
+            a.B.RT = a.B.G = 1;
+            a.B.ntiles = t0;
+            return;
+        }
+    }
     // LDS window: the (z, t) planes that the 64 sites of a block lie in
     int ws = 0;
     for (int l = 0; l < a.B.nlat; ++l) {
@@ -722,6 +753,7 @@ fl_status fl_apply_schur(fl_ctx *c, const double *in, double *out, int nrhs, int
         sb.bh[0] = (const double2 *)be;
         sb.xh[0] = (double2 *)xe;
         sb.bnorm.assign(n, 1.0);
+        sb.same_bits = true;
         if ((e = schur_apply_batch(sb, *p, dagger != 0))) return e;
         if ((e = hip_check(c, hipMemsetAsync(xo, 0, fb, c->stream), "memset"))) return e;
         launch_eo_to_canon((double2 *)xe, (double2 *)xo, cout, g, n, c->stream);
@@ -769,7 +801,7 @@ fl_status fl_solve(fl_ctx *c, const double *b, double *x, int nrhs, const fl_sol
         std::vector<double> b2;
         if ((e = norms64(c, n, be, bo, b2))) return e;
         // bhat_e = b_e + k H_eo b_o
-        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false);
+        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false, p->truncated != 0);
         SolveBatch sb;
         sb.nlat = 1;
         sb.ctx[0] = c;
@@ -782,7 +814,7 @@ fl_status fl_solve(fl_ctx *c, const double *b, double *x, int nrhs, const fl_sol
         fl_status se = solve_schur_batch(sb, *p, res);
         if (se != FL_OK && se != FL_ERR_NOCONV && se != FL_ERR_BREAKDOWN) return se;
         // x_o = b_o + k H_oe x_e
-        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false);
+        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false, p->truncated != 0);
         // stopping rule on the full operator: r = b - D x
         std::vector<double> r2;
         if ((e = full_residual2(c, n, be, bo, xe, xo, r2))) return e;
@@ -849,7 +881,7 @@ fl_status fl_loops_exact_sites(fl_ctx *c, const long long *sites, long long nsit
         if ((e = hip_check(c, hipMemsetAsync(be, 0, fb, c->stream), "memset"))) return e;
         if ((e = hip_check(c, hipMemsetAsync(bo, 0, fb, c->stream), "memset"))) return e;
         launch_point_sources((double2 *)be, (double2 *)bo, dsites + s0, ns, g, c->stream);
-        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false);
+        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false, p->truncated != 0);
         SolveBatch sb;
         sb.nlat = 1;
         sb.ctx[0] = c;
@@ -861,7 +893,7 @@ fl_status fl_loops_exact_sites(fl_ctx *c, const long long *sites, long long nsit
         fl_status se = solve_schur_batch(sb, *p, res);
         if (se != FL_OK && se != FL_ERR_NOCONV && se != FL_ERR_BREAKDOWN) return se;
         // acceptance on the full operator (point sources: |b| = 1)
-        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false);  // x_o = b_o + k H_oe x_e
+        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false, p->truncated != 0);  // x_o = b_o + k H_oe x_e
         std::vector<double> r2;
         if ((e = full_residual2(c, n, be, bo, xe, xo, r2))) return e;
         const double secs = now_s() - t_batch;
@@ -1035,6 +1067,7 @@ fl_status fl_loops_stochastic_multi(fl_ctx **ctxs, int nctx, const fl_noise_para
             const double t_batch = now_s();
             // every lattice takes part in the batch (possibly with no rhs)
             SolveBatch sb;
+            sb.same_bits = true;
             sb.nlat = 0;
             std::vector<int> lat_of;
             for (int l = 0; l < nctx; ++l) {
@@ -1074,7 +1107,7 @@ fl_status fl_loops_stochastic_multi(fl_ctx **ctxs, int nctx, const fl_noise_para
                 LatGeom g = lat_geom(c, n);
                 launch_noise_sources((double2 *)be, (double2 *)bo, nbt, g, st);
                 if ((e = norms64(c, n, be, bo, bn[l]))) return e;
-                hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false);
+                hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false, true);
             }
             for (int l = 0; l < nctx; ++l)
                 for (int k = 0; k < nr[l]; ++k) sb.bnorm.push_back(std::sqrt(bn[l][k]));
@@ -1090,7 +1123,7 @@ fl_status fl_loops_stochastic_multi(fl_ctx **ctxs, int nctx, const fl_noise_para
                 void *be = c->pool[WS_BE].p, *bo = c->pool[WS_BO].p, *xe = c->pool[WS_XE].p;
                 void *xo = ws_get(c, WS_XO, fb);
                 if (!xo) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
-                hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false);  // x_o = eta_o + k H_oe x_e
+                hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false, true);  // x_o = eta_o + k H_oe x_e
                 // statistics; solves that are not truncated are accepted on the
                 // full operator
                 std::vector<double> r2;
@@ -1430,7 +1463,7 @@ static fl_status bench_impl(fl_ctx *c, LinkFormat fmt, int nrhs, int nrep, int n
     {
         int saved = c->tune_lds[fmt];
         if (lds >= 0) c->tune_lds[fmt] = lds;
-        dslash_config(c, fmt, a);
+        dslash_config(c, fmt, a, rt <= 0 && lds < 0);
         c->tune_lds[fmt] = saved;
     }
     if (lds > a.lds) {

@@ -32,19 +32,289 @@ __device__ __forceinline__ cx<R> cpx_of(const double *v)
     return cx<R>{(R)v[0], (R)v[1]};
 }
 
+// ---------------------------------------------------------------------------
+// per-system scalar steps: the partials of a slot are summed in a fixed order,
+// then the recurrence advances
+// ---------------------------------------------------------------------------
+
+// a b + c d with the rounding written down: the scalar steps have the same bits
+// in a launch of their own and inside a vector kernel
+__device__ __forceinline__ double dot2(double a, double b, double c, double d) { return fma(a, b, c * d); }
+
+// one step of a system's scalar recurrence on a local copy of its state
+template <int STEP>
+__device__ __forceinline__ void scal_step(int stamp, int carried_r, const double P[6], SysState &s, int &act)
+{
+    switch (STEP) {
+    case SC_ALPHA: {
+        double den = dot2(P[0], P[0], P[1], P[1]);
+        if (!(den > 0) || !finite_d(den)) {
+            s.flags |= ST_BREAK;
+            act = 0;
+            break;
+        }
+        // alpha = rho / r0v
+        s.alpha[0] = dot2(s.rho[0], P[0], s.rho[1], P[1]) / den;
+        s.alpha[1] = dot2(s.rho[1], P[0], -s.rho[0], P[1]) / den;
+        break;
+    }
+    case SC_OMEGA: {
+        double tt = P[2];
+        if (tt > 0 && finite_d(tt)) {
+            s.omega[0] = P[0] / tt;
+            s.omega[1] = P[1] / tt;
+        } else if (tt == 0) {
+            s.omega[0] = s.omega[1] = 0;
+        } else {
+            s.flags |= ST_BREAK;
+            act = 0;
+        }
+        break;
+    }
+    case SC_BETA: {
+        // slots of their own: the kernel that forms r may still be reading the
+        // omega step's sums (slots 0 to 2)
+        double rho_n[2] = {P[3], P[4]};
+        double rr = P[5];
+        s.iter += 1;
+        if (!finite_d(rr) || !finite_d(rho_n[0]) || !finite_d(rho_n[1])) {
+            s.flags |= ST_BREAK;
+            act = 0;
+            break;
+        }
+        s.rr = rr;
+        if (rr > s.rmax2) s.rmax2 = rr;
+        if (rr < s.delta2 * s.rmax2) s.flags |= ST_WANT_UPD;
+        if (rr <= s.stop2) {
+            s.flags |= ST_CONV_ITER;
+            act = 0;
+        } else if (s.iter >= s.max_iter) {
+            s.flags |= ST_MAXIT;
+            act = 0;
+        }
+        double om2 = dot2(s.omega[0], s.omega[0], s.omega[1], s.omega[1]);
+        double rh2 = dot2(s.rho[0], s.rho[0], s.rho[1], s.rho[1]);
+        if (act && (!(om2 > 0) || !(rh2 > 0))) {
+            s.flags |= ST_BREAK;
+            act = 0;
+        }
+        if (om2 > 0 && rh2 > 0) {
+            // beta = (rho_n / rho) * (alpha / omega)
+            double q[2] = {dot2(rho_n[0], s.rho[0], rho_n[1], s.rho[1]) / rh2,
+                           dot2(rho_n[1], s.rho[0], -rho_n[0], s.rho[1]) / rh2};
+            double w[2] = {dot2(s.alpha[0], s.omega[0], s.alpha[1], s.omega[1]) / om2,
+                           dot2(s.alpha[1], s.omega[0], -s.alpha[0], s.omega[1]) / om2};
+            s.beta[0] = dot2(q[0], w[0], -q[1], w[1]);
+            s.beta[1] = dot2(q[0], w[1], q[1], w[0]);
+        }
+        s.rho[0] = rho_n[0];
+        s.rho[1] = rho_n[1];
+        break;
+    }
+    case SC_RESET:
+        s.tr2 = P[2];
+        s.rho[0] = P[3];
+        s.rho[1] = P[4];
+        s.rr = P[5];
+        s.rmax2 = P[5];
+        s.flags &= ~(ST_CONV_ITER | ST_WANT_UPD);
+        break;
+    case SC_INIT:
+        s.rho[0] = P[3];
+        s.rho[1] = P[4];
+        s.rr = P[5];
+        s.rmax2 = P[5];
+        s.flags = 0;
+        s.alpha[0] = s.omega[0] = 1;
+        s.alpha[1] = s.omega[1] = 0;
+        s.beta[0] = s.beta[1] = 0;
+        if (P[5] <= s.stop2) {
+            s.flags |= ST_CONV_ITER;
+            act = 0;
+        } else {
+            act = 1;
+        }
+        break;
+    case SC_CG_INIT:  // slot 2: |z|^2 with z = Dhat^+ r; slot 5: |r|^2
+        s.zz = P[2];
+        s.rr = P[5];
+        s.beta[0] = s.beta[1] = 0;
+        s.flags &= ST_MAXIT;
+        if (P[5] <= s.stop2 || !(P[2] > 0)) {
+            s.flags |= ST_CONV_ITER;
+            act = 0;
+        } else {
+            act = 1;
+        }
+        break;
+    case SC_CG_ALPHA:  // slot 2: |q|^2 with q = Dhat p
+        if (!(P[2] > 0) || !finite_d(P[2])) {
+            s.flags |= ST_BREAK;
+            act = 0;
+        } else {
+            s.alpha[0] = s.zz / P[2];
+        }
+        break;
+    case SC_CG_BETA: {  // slot 3: |z'|^2 of the updated z = Dhat^+ r (slot 2 may still be read
+                        // for alpha while z is formed); slot 5: |r|^2 if carried
+        // Without a carried r: |r - alpha q|^2 = |r|^2 - 2 alpha Re<q, r>
+        // + alpha^2 |q|^2 with <q, r> = <p, Dhat^+ r> = <p, z> = |z|^2 (CG;
+        // restored at every residual replacement) and alpha = |z|^2 / |q|^2.
+        // The recurrence holds to the rounding of the low-precision operator
+        // relative to |r|^2 at the last replacement, so below 1e-6 of that
+        // value it is no longer trusted: it still asks for a replacement
+        // (far below the delta trigger) but claims no convergence
+        double zn = P[3], rr = carried_r ? P[5] : fma(-s.alpha[0], s.zz, s.rr);
+        const bool trusted = carried_r || rr > 1e-6 * s.rmax2;
+        s.xstamp = stamp;  // r moved by alpha q in this iteration: x moves by alpha p
+        s.iter += 1;
+        s.rr = rr;
+        if (!finite_d(zn) || !finite_d(rr)) {
+            s.flags |= ST_BREAK;
+            act = 0;
+            break;
+        }
+        s.beta[0] = zn / s.zz;
+        s.zz = zn;
+        if (rr > s.rmax2) s.rmax2 = rr;
+        if (rr < s.delta2 * s.rmax2 || !trusted) s.flags |= ST_WANT_UPD;
+        if (trusted && rr <= s.stop2) {
+            s.flags |= ST_CONV_ITER;
+            act = 0;
+        } else if (s.iter >= s.max_iter) {
+            s.flags |= ST_MAXIT;
+            act = 0;
+        }
+        break;
+    }
+    case SC_CG_REZ: {  // after a residual replacement that keeps p: slot 2 |z|^2, z = Dhat^+ r;
+                       // slots 0, 1 <z, p>; slot 5 |r|^2
+        // CG's step length alpha = |z|^2 / |Dhat p|^2 assumes <z, p> = |z|^2,
+        // which holds for the iteration's own z but not for the replaced one;
+        // p += c z with c = (|z|^2 - <z, p>) / |z|^2 restores it
+        s.zz = P[2];
+        s.rr = P[5];
+        s.rmax2 = P[5];
+        s.flags &= ~(ST_CONV_ITER | ST_WANT_UPD);
+        const double zz = P[2] > 0 ? P[2] : 1.0;
+        s.beta[0] = (P[2] - P[0]) / zz;
+        s.beta[1] = -P[1] / zz;
+        if (!(P[2] > 0) || !finite_d(P[2])) {
+            s.flags |= ST_BREAK;
+            act = 0;
+        }
+        break;
+    }
+    default: break;
+    }
+}
+
+// the partial-sum slots each scalar step reads (bit k: slot k)
+constexpr int scal_slots(int step)
+{
+    switch (step) {
+    case SC_ALPHA: return 0x03;     // <r0, v>
+    case SC_OMEGA: return 0x07;     // <t, s>, |t|^2
+    case SC_BETA: return 0x38;      // <r0, r>, |r|^2
+    case SC_RESET: return 0x3c;     // |rh|^2, <r0, r>, |r|^2
+    case SC_INIT: return 0x38;      // <r0, r>, |r|^2
+    case SC_CG_INIT: return 0x24;   // |z|^2, |r|^2
+    case SC_CG_ALPHA: return 0x04;  // |q|^2
+    case SC_CG_BETA: return 0x28;   // |z|^2, |r|^2 (if carried)
+    case SC_CG_REZ: return 0x27;    // <z, p>, |z|^2, |r|^2
+    default: return 0x3f;
+    }
+}
+
+// the scalar step of one system by every wave that needs its result
+template <int STEP>
+__device__ __forceinline__ void folded_step(const BlasArgs &a, int sys, int nsb, SysState &s, int &act)
+{
+    double P[6];
+#pragma unroll
+    for (int slot = 0; slot < 6; ++slot)
+        P[slot] = (scal_slots(STEP) >> slot) & 1 ? slot_sum(a.partial, slot, a.nsys, sys, a.B.nsb_max, nsb) : 0.0;
+    s = a.st[sys];
+    act = 1;
+    scal_step<STEP>(a.stamp, a.carried_r, P, s, act);
+    // not to be contracted into the vector arithmetic
+    asm volatile("" : "+v"(s.alpha[0]), "+v"(s.alpha[1]), "+v"(s.omega[0]), "+v"(s.omega[1]), "+v"(s.beta[0]), "+v"(s.beta[1]));
+}
+
+// the state of one system as one store instruction of 8-byte words, one per
+// lane, through this wave's copy in LDS
+__device__ __forceinline__ void store_state(SysState *dst, const SysState &s, SysState *sh)
+{
+    constexpr int NW = (int)(sizeof(SysState) / 8);
+    const int lane = threadIdx.x % FL_WAVE;
+    if (lane == 0) *sh = s;
+    if (lane < NW) {
+        unsigned long long w;
+        __builtin_memcpy(&w, (const char *)sh + 8 * lane, 8);
+        ((unsigned long long *)dst)[lane] = w;
+    }
+    store_drain();
+}
+
+__device__ __forceinline__ void store_flag(int *dst, int v)
+{
+    if (threadIdx.x % FL_WAVE == 0) *dst = v;
+    store_drain();
+}
+
 // S: storage format of the iteration vectors, arithmetic in SpinorFmt<S>::R
-template <typename S, int OP>
+template <typename S, int OP, bool FOLD = false>
 __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024) void k_blas(BlasArgs a)
 {
     typedef typename SpinorFmt<S>::R R;
     TileInfo T = tile_info(a.B);
     if (!T.valid_rhs) return;
-    if (OP == OP_CG_PX) {
+    SysState fs;   // FOLD: this system's state after the scalar step
+    int fact = 1;  // FOLD: still active after it
+    if constexpr (FOLD) {
+        constexpr int STEP = OP == OP_BICG_S ? SC_ALPHA : OP == OP_BICG_XR ? SC_OMEGA : OP == OP_BICG_P ? SC_BETA
+                           : OP == OP_CG_R ? SC_CG_ALPHA : SC_CG_BETA;
+        constexpr bool BETA = STEP == SC_BETA || STEP == SC_CG_BETA;
+        const bool first = T.sb == 0;  // the wave that records the step
+        __shared__ SysState shs[16];   // a copy per wave
+        SysState *sh = shs + threadIdx.x / FL_WAVE;
+        if (!a.active[T.sys]) {
+            // a wave that finds the flag taken back by the first one in this
+            // launch (alpha, omega) stops like it
+            if (BETA && first) {
+                store_state(a.st_out + T.sys, a.st[T.sys], sh);
+                store_flag(a.act_out + T.sys, 0);
+            }
+            return;
+        }
+        folded_step<STEP>(a, T.sys, a.B.lat[T.lat].nsb, fs, fact);
+        if (first) {
+            if (BETA) {
+                store_state(a.st_out + T.sys, fs, sh);
+                store_flag(a.act_out + T.sys, fact);
+            } else {
+                // only what no other wave of this launch reads: alpha or
+                // omega, the flags, and the active flag of a breakdown
+                double *dst = STEP == SC_OMEGA ? a.st[T.sys].omega : a.st[T.sys].alpha;
+                const double *v = STEP == SC_OMEGA ? fs.omega : fs.alpha;
+                const int lane = threadIdx.x % FL_WAVE;
+                const double w = lane == 0 ? v[0] : v[1];
+                if (lane < 2) dst[lane] = w;
+                store_drain();
+                if (!fact) {
+                    store_flag(&a.st[T.sys].flags, fs.flags);
+                    store_flag(a.active + T.sys, 0);
+                }
+            }
+        }
+        if (!fact && OP != OP_CG_PX) return;
+    } else if (OP == OP_CG_PX) {
         // a system that stopped in this iteration still owes its x update
         if (!a.mask[T.sys] && a.st[T.sys].xstamp != a.stamp) return;
     } else if (a.mask && !a.mask[T.sys]) {
         return;
     }
+    const SysState &cur = FOLD ? fs : a.st[T.sys];
     const LatGeom &g = a.B.lat[T.lat];
     const int l = T.lat, i = T.site, Vh = g.Vh;
     const int rhs = __builtin_amdgcn_readfirstlane(T.rhs);
@@ -53,7 +323,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
     R q0 = 0, q1 = 0, q2 = 0;
     if (T.valid_site) {
         if (OP == OP_BICG_S) {
-            const SysState &st = a.st[T.sys];
+            const SysState &st = cur;
             cx<R> al = cpx_of<R>(st.alpha);
             cx<R> r[12], v[12];
             F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, r);
@@ -62,7 +332,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             for (int k = 0; k < 12; ++k) r[k] = cmsub(r[k], al, v[k]);
             store_result<S>(fbuf<S>(a.f[2][l], g, rhs), Vh, i, r);
         } else if (OP == OP_BICG_XR) {
-            const SysState &st = a.st[T.sys];
+            const SysState &st = cur;
             cx<R> al = cpx_of<R>(st.alpha), om = cpx_of<R>(st.omega);
             cx<R> x[12], p[12], s[12], t[12], r0[12];
             F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, x);
@@ -85,7 +355,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
                 q2 += s[k].re * s[k].re + s[k].im * s[k].im;
             }
         } else if (OP == OP_BICG_P) {
-            const SysState &st = a.st[T.sys];
+            const SysState &st = cur;
             cx<R> be = cpx_of<R>(st.beta), om = cpx_of<R>(st.omega);
             cx<R> p[12], r[12], v[12];
             F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
@@ -169,7 +439,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             for (int k = 0; k < 12; ++k) p[k] = cmad(p[k], c, z[k]);
             store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
         } else if (OP == OP_CG_R) {
-            const R al = (R)a.st[T.sys].alpha[0];
+            const R al = (R)cur.alpha[0];
             cx<R> r[12], q[12];
             F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, r);
             F::load(fbuf<S>(a.f[1][l], g, rhs), Vh, i, q);
@@ -188,8 +458,8 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
         } else if (OP == OP_CG_PX) {
             // wave-uniform: one wave is one system
-            const SysState &st = a.st[T.sys];
-            const bool xu = st.xstamp == a.stamp, pu = a.mask[T.sys] != 0;
+            const SysState &st = cur;
+            const bool xu = FOLD || st.xstamp == a.stamp, pu = FOLD ? fact != 0 : a.mask[T.sys] != 0;
             cx<R> p[12];
             F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
             if (xu) {
@@ -220,6 +490,17 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
 template <typename S>
 void dispatch(const BlasArgs &a, dim3 grid, dim3 block, hipStream_t s)
 {
+    if (a.fold) {
+        switch (a.op) {
+        case OP_BICG_S: hipLaunchKernelGGL((k_blas<S, OP_BICG_S, true>), grid, block, 0, s, a); break;
+        case OP_BICG_XR: hipLaunchKernelGGL((k_blas<S, OP_BICG_XR, true>), grid, block, 0, s, a); break;
+        case OP_BICG_P: hipLaunchKernelGGL((k_blas<S, OP_BICG_P, true>), grid, block, 0, s, a); break;
+        case OP_CG_R: hipLaunchKernelGGL((k_blas<S, OP_CG_R, true>), grid, block, 0, s, a); break;
+        case OP_CG_PX: hipLaunchKernelGGL((k_blas<S, OP_CG_PX, true>), grid, block, 0, s, a); break;
+        default: launch_unsupported("vector operation with a scalar step"); break;
+        }
+        return;
+    }
     switch (a.op) {
     case OP_BICG_S: hipLaunchKernelGGL((k_blas<S, OP_BICG_S>), grid, block, 0, s, a); break;
     case OP_BICG_XR: hipLaunchKernelGGL((k_blas<S, OP_BICG_XR>), grid, block, 0, s, a); break;
@@ -235,194 +516,6 @@ void dispatch(const BlasArgs &a, dim3 grid, dim3 block, hipStream_t s)
     case OP_DOT: hipLaunchKernelGGL((k_blas<S, OP_DOT>), grid, block, 0, s, a); break;
     case OP_CG_FIXP: hipLaunchKernelGGL((k_blas<S, OP_CG_FIXP>), grid, block, 0, s, a); break;
     default: launch_unsupported("vector operation"); break;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// per-system scalar steps: one workgroup per system sums the partials of
-// the six slots in a fixed order, then lane 0 advances the recurrence
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool finite_d(double v) { return v == v && v - v == 0.0; }
-
-// one step of a system's scalar recurrence on a local copy of its state
-template <int STEP>
-__device__ __forceinline__ void scal_step(const ScalArgs &a, const double P[6], SysState &s, int &act)
-{
-    switch (STEP) {
-    case SC_ALPHA: {
-        double den = P[0] * P[0] + P[1] * P[1];
-        if (!(den > 0) || !finite_d(den)) {
-            s.flags |= ST_BREAK;
-            act = 0;
-            break;
-        }
-        // alpha = rho / r0v
-        s.alpha[0] = (s.rho[0] * P[0] + s.rho[1] * P[1]) / den;
-        s.alpha[1] = (s.rho[1] * P[0] - s.rho[0] * P[1]) / den;
-        break;
-    }
-    case SC_OMEGA: {
-        double tt = P[2];
-        if (tt > 0 && finite_d(tt)) {
-            s.omega[0] = P[0] / tt;
-            s.omega[1] = P[1] / tt;
-        } else if (tt == 0) {
-            s.omega[0] = s.omega[1] = 0;
-        } else {
-            s.flags |= ST_BREAK;
-            act = 0;
-        }
-        break;
-    }
-    case SC_BETA: {
-        double rho_n[2] = {P[0], P[1]};
-        double rr = P[2];
-        s.iter += 1;
-        if (!finite_d(rr) || !finite_d(rho_n[0]) || !finite_d(rho_n[1])) {
-            s.flags |= ST_BREAK;
-            act = 0;
-            break;
-        }
-        s.rr = rr;
-        if (rr > s.rmax2) s.rmax2 = rr;
-        if (rr < s.delta2 * s.rmax2) s.flags |= ST_WANT_UPD;
-        if (rr <= s.stop2) {
-            s.flags |= ST_CONV_ITER;
-            act = 0;
-        } else if (s.iter >= s.max_iter) {
-            s.flags |= ST_MAXIT;
-            act = 0;
-        }
-        double om2 = s.omega[0] * s.omega[0] + s.omega[1] * s.omega[1];
-        double rh2 = s.rho[0] * s.rho[0] + s.rho[1] * s.rho[1];
-        if (act && (!(om2 > 0) || !(rh2 > 0))) {
-            s.flags |= ST_BREAK;
-            act = 0;
-        }
-        if (om2 > 0 && rh2 > 0) {
-            // beta = (rho_n / rho) * (alpha / omega)
-            double q[2] = {(rho_n[0] * s.rho[0] + rho_n[1] * s.rho[1]) / rh2,
-                           (rho_n[1] * s.rho[0] - rho_n[0] * s.rho[1]) / rh2};
-            double w[2] = {(s.alpha[0] * s.omega[0] + s.alpha[1] * s.omega[1]) / om2,
-                           (s.alpha[1] * s.omega[0] - s.alpha[0] * s.omega[1]) / om2};
-            s.beta[0] = q[0] * w[0] - q[1] * w[1];
-            s.beta[1] = q[0] * w[1] + q[1] * w[0];
-        }
-        s.rho[0] = rho_n[0];
-        s.rho[1] = rho_n[1];
-        break;
-    }
-    case SC_RESET:
-        s.tr2 = P[2];
-        s.rho[0] = P[3];
-        s.rho[1] = P[4];
-        s.rr = P[5];
-        s.rmax2 = P[5];
-        s.flags &= ~(ST_CONV_ITER | ST_WANT_UPD);
-        break;
-    case SC_INIT:
-        s.rho[0] = P[3];
-        s.rho[1] = P[4];
-        s.rr = P[5];
-        s.rmax2 = P[5];
-        s.flags = 0;
-        s.alpha[0] = s.omega[0] = 1;
-        s.alpha[1] = s.omega[1] = 0;
-        s.beta[0] = s.beta[1] = 0;
-        if (P[5] <= s.stop2) {
-            s.flags |= ST_CONV_ITER;
-            act = 0;
-        } else {
-            act = 1;
-        }
-        break;
-    case SC_CG_INIT:  // slot 2: |z|^2 with z = Dhat^+ r; slot 5: |r|^2
-        s.zz = P[2];
-        s.rr = P[5];
-        s.beta[0] = s.beta[1] = 0;
-        s.flags &= ST_MAXIT;
-        if (P[5] <= s.stop2 || !(P[2] > 0)) {
-            s.flags |= ST_CONV_ITER;
-            act = 0;
-        } else {
-            act = 1;
-        }
-        break;
-    case SC_CG_ALPHA:  // slot 2: |q|^2 with q = Dhat p
-        if (!(P[2] > 0) || !finite_d(P[2])) {
-            s.flags |= ST_BREAK;
-            act = 0;
-        } else {
-            s.alpha[0] = s.zz / P[2];
-        }
-        break;
-    case SC_CG_BETA: {  // slot 2: |z'|^2 of the updated z = Dhat^+ r; slot 5: |r|^2 if carried
-        // Without a carried r: |r - alpha q|^2 = |r|^2 - 2 alpha Re<q, r>
-        // + alpha^2 |q|^2 with <q, r> = <p, Dhat^+ r> = <p, z> = |z|^2 (CG;
-        // restored at every residual replacement) and alpha = |z|^2 / |q|^2.
-        // The recurrence holds to the rounding of the low-precision operator
-        // relative to |r|^2 at the last replacement, so below 1e-6 of that
-        // value it is no longer trusted: it still asks for a replacement
-        // (far below the delta trigger) but claims no convergence
-        double zn = P[2], rr = a.carried_r ? P[5] : s.rr - s.alpha[0] * s.zz;
-        const bool trusted = a.carried_r || rr > 1e-6 * s.rmax2;
-        s.xstamp = a.stamp;  // r moved by alpha q in this iteration: x moves by alpha p
-        s.iter += 1;
-        s.rr = rr;
-        if (!finite_d(zn) || !finite_d(rr)) {
-            s.flags |= ST_BREAK;
-            act = 0;
-            break;
-        }
-        s.beta[0] = zn / s.zz;
-        s.zz = zn;
-        if (rr > s.rmax2) s.rmax2 = rr;
-        if (rr < s.delta2 * s.rmax2 || !trusted) s.flags |= ST_WANT_UPD;
-        if (trusted && rr <= s.stop2) {
-            s.flags |= ST_CONV_ITER;
-            act = 0;
-        } else if (s.iter >= s.max_iter) {
-            s.flags |= ST_MAXIT;
-            act = 0;
-        }
-        break;
-    }
-    case SC_CG_REZ: {  // after a residual replacement that keeps p: slot 2 |z|^2, z = Dhat^+ r;
-                       // slots 0, 1 <z, p>; slot 5 |r|^2
-        // CG's step length alpha = |z|^2 / |Dhat p|^2 assumes <z, p> = |z|^2,
-        // which holds for the iteration's own z but not for the replaced one;
-        // p += c z with c = (|z|^2 - <z, p>) / |z|^2 restores it
-        s.zz = P[2];
-        s.rr = P[5];
-        s.rmax2 = P[5];
-        s.flags &= ~(ST_CONV_ITER | ST_WANT_UPD);
-        const double zz = P[2] > 0 ? P[2] : 1.0;
-        s.beta[0] = (P[2] - P[0]) / zz;
-        s.beta[1] = -P[1] / zz;
-        if (!(P[2] > 0) || !finite_d(P[2])) {
-            s.flags |= ST_BREAK;
-            act = 0;
-        }
-        break;
-    }
-    default: break;
-    }
-}
-
-// the partial-sum slots each scalar step reads (bit k: slot k)
-constexpr int scal_slots(int step)
-{
-    switch (step) {
-    case SC_ALPHA: return 0x03;     // <r0, v>
-    case SC_OMEGA: return 0x07;     // <t, s>, |t|^2
-    case SC_BETA: return 0x07;      // <r0, r>, |r|^2
-    case SC_RESET: return 0x3c;     // |rh|^2, <r0, r>, |r|^2
-    case SC_INIT: return 0x38;      // <r0, r>, |r|^2
-    case SC_CG_INIT: return 0x24;   // |z|^2, |r|^2
-    case SC_CG_ALPHA: return 0x04;  // |q|^2
-    case SC_CG_BETA: return 0x24;   // |z|^2, |r|^2 (if carried)
-    case SC_CG_REZ: return 0x27;    // <z, p>, |z|^2, |r|^2
-    default: return 0x3f;
     }
 }
 
@@ -485,7 +578,7 @@ __global__ __launch_bounds__(256) void k_scal(ScalArgs a)
     if (threadIdx.x == 0) {
         SysState s = snew;
         int act = act0;
-        scal_step<STEP>(a, P, s, act);
+        scal_step<STEP>(a.stamp, a.carried_r, P, s, act);
         snew = s;
         if (act != act0) a.active[sys] = act;
     }

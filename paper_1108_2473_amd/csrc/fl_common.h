@@ -1010,6 +1010,24 @@ __device__ __forceinline__ size_t pidx(int slot, int nsys, int sys, int nsb_max,
     return ((size_t)slot * nsys + sys) * nsb_max + sb;
 }
 
+__device__ __forceinline__ bool finite_d(double v) { return v == v && v - v == 0.0; }
+
+// the partial sums of a slot for one system by one wave, in the order of a
+// halving tree over 256 threads that stride over the site blocks
+__device__ __forceinline__ double slot_sum(const double *partial, int slot, int nsys, int sys, int nb, int nsb)
+{
+    const double *q = partial + pidx(slot, nsys, sys, nb, 0);
+    double r[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int s0 = threadIdx.x % FL_WAVE; s0 < nsb; s0 += 256) {
+        double v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = q[min(s0 + 64 * k, nsb - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] += s0 + 64 * k < nsb ? v[k] : 0.0;
+    }
+    return wave_sum((r[0] + r[2]) + (r[1] + r[3]));
+}
+
 // A wave's sums s0, s1, s2 (equal in every lane) as a single store
 // instruction at the end of a kernel: lane k < 3 writes slot slot0 + k when
 // bit k of `which` is set.

@@ -61,7 +61,7 @@ __device__ __forceinline__ void load_once(const Buf &b, int Vh, int i, cx<R> s[1
 // The reductions use the values as stored (after any rounding of the format).
 template <typename S, int EPI, typename R>
 __device__ __forceinline__ void epilogue(const DslashArgs &a, const TileInfo &T, const LatGeom &g, int rhs,
-                                         const cx<R> acc[12], R &q0, R &q1, R &q2)
+                                         const cx<R> acc[12], R &q0, R &q1, R &q2, double alpha = 0.0)
 {
     typedef SpinorFmt<S> F;
     const R cb = (R)a.cb[T.lat];
@@ -92,7 +92,7 @@ __device__ __forceinline__ void epilogue(const DslashArgs &a, const TileInfo &T,
         // out = y - alpha (x + cb acc), y the field this launch overwrites (own site only)
         cx<R> yv[12];
         load_once<S, R>(spinor_buf<S>(a.y[T.lat], g.Vh, rhs), g.Vh, T.site, yv);
-        const R al = (R)a.st[T.sys].alpha[0];
+        const R al = (R)(a.fold ? alpha : a.st[T.sys].alpha[0]);
 #pragma unroll
         for (int k = 0; k < 12; ++k) out[k] = cx<R>{fma(-al, out[k].re, yv[k].re), fma(-al, out[k].im, yv[k].im)};
     }
@@ -505,6 +505,161 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
     reduce_partials<EPI>(a, T, q0, q1, q2);
 }
 
+// ---------------------------------------------------------------------------
+// Small grids (lds mode 5): a workgroup computes 64 sites of ONE right-hand
+// side, a wave per hop.  Each wave loads one neighbour spinor and one link and
+// leaves the projected product in LDS; the first wave adds the eight products
+// in the order of hop_site and runs the epilogue.  With fewer tiles than the
+// chip holds waves the hop's time is one wave's chain of loads: eight round
+// trips become one (16-bit, 8^3x16, one right-hand side: a whole CGNR solve
+// 4.69 -> 3.51 ms).  16-bit results equal the other kernels' bit for bit; in
+// FP64 and FP32 those contract the sum into the products, which can't be done here.
+// ---------------------------------------------------------------------------
+template <typename S, class LK>
+struct SplitHop {
+    typedef typename SpinorFmt<S>::R R;
+    // the product of direction slot D and the factor it is added with, but for the boundary sign
+    template <int D, bool DAG>
+    __device__ static __forceinline__ R product(const Buf &in, const Buf &gauge, int Vh, int par, int i, int nb,
+                                                cx<R> w[6])
+    {
+        constexpr int MU = D >> 1;
+        constexpr int SGN = (D & 1) ? (DAG ? -1 : 1) : (DAG ? 1 : -1);
+        cx<R> psi[12], h[6], U[3][3];
+        const R f = SpinorFmt<S>::load_raw(in, Vh, nb, psi);
+        const int lp = (D & 1) ? 1 - par : par;
+        link_load<LK>(gauge, Vh, (MU * 2 + lp) * LK::NC * Vh * LK::ESZ, (D & 1) ? nb : i, U);
+        project<MU, SGN>(psi, h);
+        if constexpr (D & 1)
+            link_adj_mul(U, h, w);
+        else
+            link_mul(U, h, w);
+        return f * LK::UNIT;
+    }
+};
+
+template <>
+struct SplitHop<H16, LinkQ16R12> {
+    typedef float R;
+    template <int D, bool DAG>
+    __device__ static __forceinline__ float product(const Buf &in, const Buf &gauge, int Vh, int par, int i, int nb,
+                                                    cx<float> w[6])
+    {
+        typedef LinkQ16R12 LK;
+        constexpr int MU = D >> 1;
+        constexpr int SGN = (D & 1) ? (DAG ? -1 : 1) : (DAG ? 1 : -1);
+        s2 psi[12], h[6];
+        unsigned L[LK::PK_SNC];
+        const float f = LK::HALF_UNIT * SpinorFmt<H16>::load_i16(in, Vh, nb, psi);
+        LK::V v[LK::NC];
+        const int lp = (D & 1) ? 1 - par : par;
+#pragma unroll
+        for (int k = 0; k < LK::NC; ++k)
+            v[k] = LK::buf_get(gauge, ((D & 1) ? nb : i) * LK::ESZ, ((MU * 2 + lp) * LK::NC + k) * Vh * LK::ESZ);
+        LK::stage_pk<(D & 1) != 0>(v, L);
+        project_i16<MU, SGN>(psi, h);
+        link_mul_i16(L, h, w);
+        return f;
+    }
+};
+
+template <typename S, class LK, bool DAG, int EPI>
+__global__ __launch_bounds__(512) void k_dslash_split(DslashArgs a)
+{
+    typedef typename SpinorFmt<S>::R R;
+    __shared__ cx<R> prod[8][6][FL_WAVE];
+    __shared__ R fac[8][FL_WAVE];
+    TileInfo T = tile_info(a.B);  // one right-hand side per workgroup: its eight waves are one tile's
+    const int d = __builtin_amdgcn_readfirstlane(threadIdx.x / FL_WAVE);
+    T.rhs -= d;
+    T.sys -= d;
+    const LatGeom &g = a.B.lat[T.lat];
+    const int rhs = __builtin_amdgcn_readfirstlane(T.rhs), sys = __builtin_amdgcn_readfirstlane(T.sys);
+    if (a.mask && !a.mask[sys]) return;
+    const int Vh = g.Vh, lane = threadIdx.x % FL_WAVE, i = T.valid_site ? T.site : Vh - 1;
+    const Coord c = cb_coords(g, a.par, i);
+    int nb[8];
+    neighbours(g, c, i, nb);
+    const Buf in = spinor_buf<S>(a.in[T.lat], Vh, rhs);
+    const Buf gauge = make_buf(a.gauge[T.lat], (unsigned)(8u * LK::NC * LK::ESZ * (unsigned)Vh));
+    // fold: alpha of this iteration, as the scalar step before this launch would set it
+    double alpha = 0.0;
+    bool broken = false;
+    if constexpr ((EPI & EPI_CGZ) != 0) {
+        if (a.fold && d == 0) {
+            const double qq = slot_sum(a.partial, 2, a.nsys, sys, a.B.nsb_max, g.nsb);
+            broken = !(qq > 0) || !finite_d(qq);
+            alpha = broken ? 0.0 : a.st[sys].zz / qq;
+        }
+    }
+    {
+        cx<R> w[6];
+        R f;
+        typedef SplitHop<S, LK> H;
+        switch (d) {
+        case 0: f = H::template product<0, DAG>(in, gauge, Vh, a.par, i, nb[0], w); break;
+        case 1: f = H::template product<1, DAG>(in, gauge, Vh, a.par, i, nb[1], w); break;
+        case 2: f = H::template product<2, DAG>(in, gauge, Vh, a.par, i, nb[2], w); break;
+        case 3: f = H::template product<3, DAG>(in, gauge, Vh, a.par, i, nb[3], w); break;
+        case 4: f = H::template product<4, DAG>(in, gauge, Vh, a.par, i, nb[4], w); break;
+        case 5: f = H::template product<5, DAG>(in, gauge, Vh, a.par, i, nb[5], w); break;
+        case 6:
+            f = H::template product<6, DAG>(in, gauge, Vh, a.par, i, nb[6], w);
+            f = (c.t + 1 == g.L[3] ? (R)g.bc_t : (R)1) * f;
+            break;
+        default:
+            f = H::template product<7, DAG>(in, gauge, Vh, a.par, i, nb[7], w);
+            f = (c.t == 0 ? (R)g.bc_t : (R)1) * f;
+            break;
+        }
+        fac[d][lane] = f;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) prod[d][k][lane] = w[k];
+    }
+    __syncthreads();
+    if (d != 0) return;
+    if constexpr ((EPI & EPI_CGZ) != 0) {
+        if (a.fold) {
+            if (T.sb == 0) {
+                if (lane == 0) {
+                    if (broken)
+                        a.st[sys].flags |= ST_BREAK;
+                    else
+                        a.st[sys].alpha[0] = alpha;
+                }
+                store_drain();
+                if (lane == 0 && broken) a.active[sys] = 0;
+                store_drain();
+            }
+            if (broken) return;
+        }
+    }
+    R q0 = 0, q1 = 0, q2 = 0;
+    if (T.valid_site) {
+        cx<R> acc[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) acc[k] = cx<R>{(R)0, (R)0};
+        constexpr int SF = DAG ? 1 : -1, SB = -SF;
+        auto add = [&](auto dd) {
+            constexpr int D = decltype(dd)::value;
+            cx<R> w[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) w[k] = prod[D][k][lane];
+            accumulate_scaled<(D >> 1), (D & 1) ? SB : SF>(acc, w, fac[D][lane]);
+        };
+        add(std::integral_constant<int, 0>());
+        add(std::integral_constant<int, 1>());
+        add(std::integral_constant<int, 2>());
+        add(std::integral_constant<int, 3>());
+        add(std::integral_constant<int, 4>());
+        add(std::integral_constant<int, 5>());
+        add(std::integral_constant<int, 6>());
+        add(std::integral_constant<int, 7>());
+        epilogue<S, EPI>(a, T, g, rhs, acc, q0, q1, q2, alpha);
+    }
+    reduce_partials<EPI>(a, T, q0, q1, q2);
+}
+
 template <typename S, class LK>
 size_t dslash_lds_bytes_t(int RT, int wsmax, int lds)
 {
@@ -524,7 +679,13 @@ constexpr size_t FP32_HOP_LDS_CAP = 70 * 1024;
 template <typename S, class LK, bool DAG, int EPI>
 void launch_one(const DslashArgs &a, dim3 grid, dim3 block, hipStream_t s)
 {
-    if (a.lds == 0) {
+    if (a.lds == 5) {
+        // the reliable updates' epilogues and bf16 links have no use for it
+        if constexpr (!(EPI & (EPI_SUBY16 | EPI_SUBY32 | EPI_ACCX)) && !std::is_same<LK, LinkBF16R12>::value)
+            hipLaunchKernelGGL((k_dslash_split<S, LK, DAG, EPI>), grid, dim3(8 * FL_WAVE), 0, s, a);
+        else
+            launch_unsupported("hopping epilogue of a small grid");
+    } else if (a.lds == 0) {
         hipLaunchKernelGGL((k_dslash<S, LK, DAG, EPI>), grid, block, 0, s, a);
     } else {
         size_t shm = dslash_lds_bytes_t<S, LK>(a.B.RT, a.wsmax, a.lds);
@@ -600,7 +761,7 @@ void dispatch_dag(const DslashArgs &a, bool dag, int epi, dim3 grid, dim3 block,
 
 size_t dslash_lds_bytes(LinkFormat fmt, int RT, int wsmax, int lds)
 {
-    if (lds == 0) return 0;
+    if (lds == 0 || lds == 5) return 0;
     switch (fmt) {
     case LINK_F64_R18: return dslash_lds_bytes_t<double, LinkF64R18>(RT, wsmax, lds);
     case LINK_F32_R18: return dslash_lds_bytes_t<float, LinkF32R18>(RT, wsmax, lds);

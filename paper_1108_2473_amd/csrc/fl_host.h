@@ -60,10 +60,13 @@ struct DslashArgs {
     const void *y[FL_MAXLAT];
     const void *gauge[FL_MAXLAT];
     double ca[FL_MAXLAT], cb[FL_MAXLAT];
+    int fold;   // EPI_CGZ, lds mode 5: alpha from the partial sums of |q|^2 (slot 2 of partial), written to st and active
+    int *active;
     int lds;    // 0: neighbours from memory; 1: x/y neighbours from an LDS window;
-                // 2: also the workgroup's links staged in LDS once
+                // 2: also the workgroup's links staged in LDS once; 4: links only;
+                // 5: a workgroup per 64 sites of one right-hand side, a wave per hop (small grids)
     int wsmax;  // LDS window length in sites (64 + 2 * max Lx/2), set by the launcher
-    const SysState *st;  // per-system scalars (EPI_CGZ)
+    SysState *st;  // per-system scalars (EPI_CGZ)
     void *w[FL_MAXLAT];  // the FP64 field of EPI_ACCX
 };
 
@@ -131,6 +134,16 @@ struct BlasArgs {
     double *partial;
     SysState *st;
     int stamp;  // iteration stamp (OP_CG_PX)
+    // fold: the scalar step before this operation (alpha for OP_BICG_S and
+    // OP_CG_R, omega for OP_BICG_XR, beta for OP_BICG_P and OP_CG_PX) is
+    // computed by every wave from the partial sums instead of a launch of its
+    // own.  A beta step leaves the new state and active flags of all systems
+    // in st_out and act_out (waves still read the old ones); mask is active
+    int fold;
+    int carried_r;
+    int *active;
+    SysState *st_out;
+    int *act_out;
     void *f[6][FL_MAXLAT];
 };
 
@@ -295,8 +308,9 @@ struct fl_ctx {
 // contents not kept; the stream is synchronised before an old block is freed)
 void *pinned_get(fl_ctx *c, size_t bytes);
 
-// LDS staging mode and window length for a hopping launch over batch B
-void dslash_config(const fl_ctx *c, LinkFormat fmt, DslashArgs &a);
+// LDS staging mode and window length for a hopping launch over batch B;
+// split_ok: the launch may become one of mode 5, which changes the tile map in a.B
+void dslash_config(const fl_ctx *c, LinkFormat fmt, DslashArgs &a, bool split_ok);
 
 fl_status set_err(fl_ctx *c, fl_status st, const std::string &msg);
 fl_status hip_check(fl_ctx *c, hipError_t e, const char *what);
@@ -310,9 +324,10 @@ BatchGeom batch_geom(fl_ctx *const *ctx, const int *nrhs, int nlat, int RT, int 
 // right-hand-side blocks per site sweep (the autotuner's choice if any)
 void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G);
 // single-lattice hopping launch on FP64 fields with the given FP64 links:
-// out = ca x + cb H in (x may be null: out = cb H in); epi < 0: XPAY if x
+// out = ca x + cb H in (x may be null: out = cb H in); epi < 0: XPAY if x;
+// split_ok as in dslash_config
 void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *in, void *out, const void *x,
-                  double ca, double cb, bool dag, int epi = -1);
+                  double ca, double cb, bool dag, int epi = -1, bool split_ok = true);
 // size of the fixed device scratch array of fl_apply_D_noalloc (MiB)
 #define FL_NOALLOC_SCRATCH_MB 64
 // takes the device address of that array on `device` (once; call with the
@@ -343,6 +358,7 @@ struct SolveBatch {
     const double2 *bh[FL_MAXLAT] = {nullptr, nullptr, nullptr, nullptr};
     double2 *xh[FL_MAXLAT] = {nullptr, nullptr, nullptr, nullptr};
     std::vector<double> bnorm;  // |b| of the full source, per system (host)
+    bool same_bits = false;     // a system's result may not depend on the rest of the batch in the last bit
 };
 
 struct SysResult {

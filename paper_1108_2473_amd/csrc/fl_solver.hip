@@ -46,6 +46,9 @@ struct PinArr {
     }
 };
 
+// largest number of 64-site tiles whose vector kernels compute the scalar steps
+constexpr int FOLD_TILES = 4096;
+
 struct Solver {
     SolveBatch &sb;
     const fl_solver_params &prm;
@@ -65,6 +68,11 @@ struct Solver {
     int stamp = 0;  // CGNR iteration stamp
     int flip = 0;   // sweep direction of the next launch (BatchGeom::rev)
     int *active = nullptr, *mask = nullptr;
+    SysState *st_alt = nullptr;  // the copy that the next folded beta step writes
+    int *act_alt = nullptr;
+    bool split = false;     // small grids: hops of the iteration with a wave per direction
+    bool fold = false;      // small grids: scalar steps inside the vector kernels
+    bool fold_cgz = false;  // and CGNR's alpha inside the hop that updates z
     PinArr<SysState> hst;
     PinArr<int> hact, hmask, hm2;  // hm2: the masks of restarts and CGNR replacements
     std::vector<long long> active_count;  // per lattice, at the last check
@@ -98,14 +106,19 @@ struct Solver {
         }
         a.B.rev = flip;
         flip ^= 1;
-        dslash_config(c0, f, a);
+        dslash_config(c0, f, a, split && lo);
+        if (epi & EPI_CGZ) {
+            a.fold = fold_cgz;
+            a.active = active;
+        }
         if (pslot >= 0) prof_begin(c0, pslot);
         launch_dslash(f, a, dag, epi, st);
         if (pslot >= 0) prof_end(c0, pslot, 0.0);
     }
 
+    // folded: with the scalar step in front of it (BlasArgs::fold)
     void blas(VecFormat f, int op, std::initializer_list<const MF *> fields, int flag, int slot0, const int *msk,
-              int pslot = -1)
+              int pslot = -1, bool folded = false)
     {
         BlasArgs a;
         std::memset(&a, 0, sizeof(a));
@@ -118,6 +131,11 @@ struct Solver {
         a.partial = partial;
         a.st = dst;
         a.stamp = stamp;
+        a.fold = folded;
+        a.carried_r = prm.truncated != 0;
+        a.active = active;
+        a.st_out = st_alt;
+        a.act_out = act_alt;
         int k = 0;
         for (const MF *f : fields) {
             for (int l = 0; l < B.nlat; ++l) a.f[k][l] = f->p[l];
@@ -128,6 +146,11 @@ struct Solver {
         if (pslot >= 0) prof_begin(c0, pslot);
         launch_blas(f, a, st);
         if (pslot >= 0) prof_end(c0, pslot, 0.0);
+        if (folded && (op == OP_BICG_P || op == OP_CG_PX)) {
+            // the new state and flags are the other copy's
+            std::swap(dst, st_alt);
+            std::swap(active, act_alt);
+        }
     }
 
     void scal(int step, const int *msk)
@@ -161,13 +184,13 @@ struct Solver {
     {
         const VecFormat lf = vf;
         schur_lo(P, V, EPI_DOTY, &R0, 0, false, FL_PROF_DSLASH);   // v = Dhat p, <r0, v>
-        scal(SC_ALPHA, nullptr);
-        blas(lf, OP_BICG_S, {&R, &V, &S}, 0, 0, active);          // s = r - alpha v
+        if (!fold) scal(SC_ALPHA, nullptr);
+        blas(lf, OP_BICG_S, {&R, &V, &S}, 0, 0, active, -1, fold);  // s = r - alpha v
         schur_lo(S, T, EPI_DOTX_NORM, nullptr, 0, false, -1, FL_PROF_DSLASH_END);  // t = Dhat s, <t, s>, |t|^2
-        scal(SC_OMEGA, nullptr);
-        blas(lf, OP_BICG_XR, {&XL, &P, &S, &T, &R, &R0}, 0, 0, active, FL_PROF_BLAS_UPDATE);
-        scal(SC_BETA, nullptr);
-        blas(lf, OP_BICG_P, {&P, &R, &V}, 0, 0, active);          // p = r + beta (p - omega v)
+        if (!fold) scal(SC_OMEGA, nullptr);
+        blas(lf, OP_BICG_XR, {&XL, &P, &S, &T, &R, &R0}, 0, 3, active, FL_PROF_BLAS_UPDATE, fold);
+        if (!fold) scal(SC_BETA, nullptr);
+        blas(lf, OP_BICG_P, {&P, &R, &V}, 0, 0, active, -1, fold);  // p = r + beta (p - omega v)
     }
 
     // CGNR on the Schur system: p, q = Dhat p and the normal residual
@@ -184,22 +207,22 @@ struct Solver {
         // q = Dhat p with |q|^2 (slot 2)
         dslash(fmt, true, 1, P, TMP, nullptr, nullptr, 1.0, nullptr, EPI_PLAIN, 0, active, false, FL_PROF_DSLASH);
         dslash(fmt, true, 0, TMP, V, &P, nullptr, 1.0, neg_k2, EPI_XPAY | EPI_NORM, 0, active, false, -1);
-        scal(SC_CG_ALPHA, nullptr);
+        if (!(prm.truncated ? fold : fold_cgz)) scal(SC_CG_ALPHA, nullptr);
         if (prm.truncated) {
-            blas(lf, OP_CG_R, {&R, &V}, 0, 3, active);  // r -= alpha q, |r|^2 -> slot 5
-            // z = Dhat^+ r with |z|^2 (slot 2)
+            blas(lf, OP_CG_R, {&R, &V}, 0, 3, active, -1, fold);  // r -= alpha q, |r|^2 -> slot 5
+            // z = Dhat^+ r with |z|^2 (slot 3)
             dslash(fmt, true, 1, R, TMP, nullptr, nullptr, 1.0, nullptr, EPI_PLAIN, 0, active, true, -1);
-            dslash(fmt, true, 0, TMP, S, &R, nullptr, 1.0, neg_k2, EPI_XPAY | EPI_NORM, 0, active, true,
+            dslash(fmt, true, 0, TMP, S, &R, nullptr, 1.0, neg_k2, EPI_XPAY | EPI_NORM, 1, active, true,
                    FL_PROF_DSLASH_END);
         } else {
-            // z -= alpha Dhat^+ q in the epilogue of the second hop, with |z|^2 (slot 2)
+            // z -= alpha Dhat^+ q in the epilogue of the second hop, with |z|^2 (slot 3)
             dslash(fmt, true, 1, V, TMP, nullptr, nullptr, 1.0, nullptr, EPI_PLAIN, 0, active, true, -1);
-            dslash(fmt, true, 0, TMP, S, &V, &S, 1.0, neg_k2, EPI_XPAY | EPI_NORM | EPI_CGZ, 0, active, true,
+            dslash(fmt, true, 0, TMP, S, &V, &S, 1.0, neg_k2, EPI_XPAY | EPI_NORM | EPI_CGZ, 1, active, true,
                    FL_PROF_DSLASH_END);
         }
-        scal(SC_CG_BETA, nullptr);
-        // x += alpha p (also for a system that stopped in SC_CG_BETA), then p = z + beta p
-        blas(lf, OP_CG_PX, {&P, &S, &XL}, 0, 0, active, FL_PROF_BLAS_UPDATE);
+        if (!fold) scal(SC_CG_BETA, nullptr);
+        // x += alpha p (also for a system that stopped in the beta step), then p = z + beta p
+        blas(lf, OP_CG_PX, {&P, &S, &XL}, 0, 0, active, FL_PROF_BLAS_UPDATE, fold);
     }
 
     // FP64 residual of the masked systems: rh = bh - Dhat xh (|rh|^2 -> slot 2),
@@ -288,6 +311,26 @@ fl_status Solver::prepare()
     nsys = 0;
     for (int l = 0; l < sb.nlat; ++l) nsys += sb.nrhs[l];
     if (nsys == 0) return FL_OK;
+    // The 16-bit hop gives the same bits with a wave per direction, the folded
+    // steps do in every precision: results don't depend on the batch.  The FP64
+    // and FP32 hops round differently, so they run a wave per direction only
+    // for fewer than 4 right-hand sides (whose FP64 hops have always differed,
+    // by their LDS windows), and never where truncated solves are compared.
+    {
+        split = fmt == LINK_Q16_R12 || (!sb.same_bits && !prm.truncated);
+        DslashArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.B = B;
+        dslash_config(c0, fmt, a, split);
+        // a folded step costs every wave a look at all the partial sums of its
+        // system, a launch of its own about 5 us: folded up to 512 site blocks
+        // (16^3x32 has 1024: 4.61 ms against 4.48 for one FP64 solve) and
+        // while the grid is small
+        int tiles = 0;
+        for (int l = 0; l < B.nlat; ++l) tiles += B.lat[l].nsb * B.lat[l].nrhs;
+        fold = B.nsb_max <= 512 && tiles <= FOLD_TILES;
+        fold_cgz = fold && a.lds == 5;
+    }
 
     // workspace
     const size_t lob = vec_site_bytes(vf);
@@ -317,8 +360,12 @@ fl_status Solver::prepare()
     partial = (double *)ws_get(c0, WS_PART, sizeof(double) * 6 * (size_t)nsys * B.nsb_max);
     // [SysState x nsys][active x nsys] in one block, laid out like the
     // page-locked host copy below, so one transfer fetches both at a check
-    dst = (SysState *)ws_get(c0, WS_STATE, (sizeof(SysState) + sizeof(int)) * nsys);
+    // (twice: a folded beta step leaves its result in the other block)
+    const size_t blk = ((sizeof(SysState) + sizeof(int)) * (size_t)nsys + 255) / 256 * 256;
+    dst = (SysState *)ws_get(c0, WS_STATE, 2 * blk);
     active = dst ? (int *)(dst + nsys) : nullptr;
+    st_alt = dst ? (SysState *)((char *)dst + blk) : nullptr;
+    act_alt = dst ? (int *)(st_alt + nsys) : nullptr;
     mask = (int *)ws_get(c0, WS_MASK, sizeof(int) * nsys);
     if (!partial || !dst || !active || !mask) return set_err(c0, FL_ERR_NOMEM, "device allocation failed");
     {

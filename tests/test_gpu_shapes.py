@@ -71,3 +71,46 @@ def test_gradient_ragged(F, dims):
     assert np.abs(dU - dUo).max() <= 1e-9 * np.abs(dUo).max()
     assert abs(dk - dko) <= 1e-9 * abs(dko)
     lat.close()
+
+
+@pytest.mark.parametrize("prec,reals", [(1, 12), (1, 18), (3, 12)])
+@pytest.mark.parametrize("solver", [0, 1])
+def test_small_grid_truncated_bits(F, prec, reals, solver):
+    """Truncated solves in the low precisions: alone on a small grid (scalar
+    steps inside the vector kernels, 16-bit hops with a wave per direction) and
+    in a batch beyond both limits (4096 and 1024 tiles) the results are equal
+    bit for bit."""
+    dims = (4, 4, 4, 6)  # 192 sites: three blocks
+    lat, _ = make(F, dims)
+    n = 1400
+    few = S.random_spinors(dims, 4, 55)  # 4: fewer use another FP64 hop around the iteration
+    b = np.ascontiguousarray(np.broadcast_to(few, (n // 4,) + few.shape)).reshape((n,) + few.shape[1:])
+    prm = F.SolverParams(inner_prec=prec, gauge_reals=reals, truncated=True, max_iter=7, solver=solver)
+    big, _ = lat.solve(b, prm, check=False)
+    small, _ = lat.solve(few, prm, check=False)
+    assert np.array_equal(big[:4], small)
+    assert np.array_equal(big[-4:], small)
+    lat.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 3])
+@pytest.mark.parametrize("solver", [0, 1])
+@pytest.mark.parametrize("dims,nrhs", [((2, 2, 2, 2), 1), ((6, 4, 2, 6), 3), ((8, 8, 8, 28), 2), ((8, 8, 8, 28), 3),
+                                       ((4, 4, 4, 6), 341), ((4, 4, 4, 6), 342)])
+def test_small_grid_solves(F, prec, solver, dims, nrhs):
+    """On both sides of the limits of the hop with a wave per direction (FP64 330
+    tiles: 224 and 336; 16-bit 1024: 1023 and 1026; FP32 up to 3 right-hand
+    sides) and down to one partly filled site block: the residual recomputed
+    with the operator meets the tolerance (rounding of the recomputation:
+    1e-14)."""
+    lat, U = make(F, dims, kappa=0.13)
+    b = S.random_spinors(dims, nrhs, 56)
+    tol = 1e-10
+    x, info = lat.solve(b, F.SolverParams(inner_prec=prec, solver=solver, tol=tol))
+    assert all(q["converged"] for q in info)
+    r = (b - lat.apply_D(x)).reshape(nrhs, -1)
+    rel = np.linalg.norm(r, axis=1) / np.linalg.norm(b.reshape(nrhs, -1), axis=1)
+    assert rel.max() <= tol + 1e-14
+    want = O.apply_D(U, x[-1:], dims, -1, 0.13)
+    assert np.linalg.norm(b[-1:] - want) <= (tol + 1e-14) * np.linalg.norm(b[-1:])
+    lat.close()
