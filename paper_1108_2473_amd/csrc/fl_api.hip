@@ -685,8 +685,12 @@ fl_status fl_apply_D(fl_ctx *c, const double *in, double *out, int nrhs, int dag
     fl_status e;
     if ((e = check_ready(c))) return e;
     hipSetDevice(c->device);
-    const int chunk = std::max(1, std::min(nrhs, default_batch(c, 1)));
     const size_t per = (size_t)c->V * 24 * sizeof(double);
+    // in one pass, unless the caller's fields share bytes (the even/odd route
+    // has read its input before it writes)
+    const bool onepass = where == FL_HOST || !fields_overlap(in, out, per * (size_t)nrhs);
+    const bool whole = onepass && where == FL_DEVICE;  // no workspace: all at once
+    const int chunk = whole ? std::max(1, nrhs) : std::max(1, std::min(nrhs, default_batch(c, 1)));
     for (int k0 = 0; k0 < nrhs; k0 += chunk) {
         int n = std::min(chunk, nrhs - k0);
         const double *src = in + (size_t)k0 * c->V * 24;
@@ -694,21 +698,27 @@ fl_status fl_apply_D(fl_ctx *c, const double *in, double *out, int nrhs, int dag
         double *cin = (double *)src, *cout = dst;
         if (where == FL_HOST) {
             cin = (double *)ws_get(c, WS_CANON, per * n);
-            cout = cin;
-            if (!cin) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
+            cout = (double *)ws_get(c, WS_BE, per * n);
+            if (!cin || !cout) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
             if ((e = hip_check(c, hipMemcpyAsync(cin, src, per * n, hipMemcpyHostToDevice, c->stream), "upload")))
                 return e;
         }
-        size_t fb = (size_t)n * c->Vh * 192;
-        void *be = ws_get(c, WS_BE, fb), *bo = ws_get(c, WS_BO, fb);
-        void *xe = ws_get(c, WS_XE, fb), *xo = ws_get(c, WS_XO, fb);
-        if (!be || !bo || !xe || !xo) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
         LatGeom g = lat_geom(c, n);
-        launch_canon_to_eo(cin, (double2 *)be, (double2 *)bo, g, n, c->stream);
-        // (D psi)_e = psi_e - k H_eo psi_o, (D psi)_o = psi_o - k H_oe psi_e
-        hop64(c, n, 0, bo, xe, be, 1.0, -c->kappa, dagger != 0);
-        hop64(c, n, 1, be, xo, bo, 1.0, -c->kappa, dagger != 0);
-        launch_eo_to_canon((double2 *)xe, (double2 *)xo, cout, g, n, c->stream);
+        if (onepass) {
+            const void *lk = links(c, LINK_F64_R18);
+            if (!lk) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
+            launch_apply_full(cin, cout, lk, g, n, c->kappa, dagger != 0, c->stream);
+        } else {
+            size_t fb = (size_t)n * c->Vh * 192;
+            void *be = ws_get(c, WS_BE, fb), *bo = ws_get(c, WS_BO, fb);
+            void *xe = ws_get(c, WS_XE, fb), *xo = ws_get(c, WS_XO, fb);
+            if (!be || !bo || !xe || !xo) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
+            launch_canon_to_eo(cin, (double2 *)be, (double2 *)bo, g, n, c->stream);
+            // (D psi)_e = psi_e - k H_eo psi_o, (D psi)_o = psi_o - k H_oe psi_e
+            hop64(c, n, 0, bo, xe, be, 1.0, -c->kappa, dagger != 0);
+            hop64(c, n, 1, be, xo, bo, 1.0, -c->kappa, dagger != 0);
+            launch_eo_to_canon((double2 *)xe, (double2 *)xo, cout, g, n, c->stream);
+        }
         if (where == FL_HOST)
             if ((e = hip_check(c, hipMemcpyAsync(dst, cout, per * n, hipMemcpyDeviceToHost, c->stream), "download")))
                 return e;

@@ -328,6 +328,15 @@ void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G);
 // split_ok as in dslash_config
 void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *in, void *out, const void *x,
                   double ca, double cb, bool dag, int epi = -1, bool split_ok = true);
+// out = (1 - kappa H) in on canonical FP64 fields that do not overlap
+void launch_apply_full(const double *in, double *out, const void *links, const LatGeom &g, int nrhs, double kappa,
+                       bool dag, hipStream_t s);
+// whether two fields of the same size share bytes
+inline bool fields_overlap(const void *a, const void *b, size_t bytes)
+{
+    const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+    return p < q + bytes && q < p + bytes;
+}
 // size of the fixed device scratch array of fl_apply_D_noalloc (MiB)
 #define FL_NOALLOC_SCRATCH_MB 64
 // takes the device address of that array on `device` (once; call with the

@@ -1,6 +1,6 @@
 // fl_noalloc.hip -- the entry point that allocates nothing: the Wilson-Dirac
-// operator on device spinors with its even/odd work fields in a fixed
-// device array of this library instead of allocated workspace.
+// operator on device spinors, in one pass; where input and result share bytes,
+// through even/odd work fields in a fixed device array of this library.
 //
 // `scratch` is a file-scope device array; each GPU the library runs on holds
 // its own copy until the process ends.  In host code its name is only a
@@ -67,8 +67,12 @@ extern "C" fl_status fl_apply_D_noalloc(fl_ctx *c, const double *in, double *out
     const void *gauge = c->gauge_ok[LINK_F64_R18] ? c->gauge[LINK_F64_R18] : nullptr;
     if (!gauge) return set_err(c, FL_ERR_STATE, "FP64 links not packed (fl_set_gauge)");
     hipSetDevice(c->device);
-    void *be = base, *bo = base + half, *xe = base + 2 * half, *xo = base + 3 * half;
     LatGeom g = lat_geom(c, nrhs);
+    if (!fields_overlap(in, out, 2 * half)) {
+        launch_apply_full(in, out, gauge, g, nrhs, c->kappa, dagger != 0, c->stream);
+        return hip_check(c, hipGetLastError(), "fl_apply_D_noalloc");
+    }
+    void *be = base, *bo = base + half, *xe = base + 2 * half, *xo = base + 3 * half;
     launch_canon_to_eo(in, (double2 *)be, (double2 *)bo, g, nrhs, c->stream);
     // (D psi)_e = psi_e - k H_eo psi_o, (D psi)_o = psi_o - k H_oe psi_e
     hop64_launch(c, gauge, nrhs, 0, bo, xe, be, 1.0, -c->kappa, dagger != 0);
