@@ -226,20 +226,62 @@ constexpr int scal_slots(int step)
     }
 }
 
-// the scalar step of one system by every wave that needs its result
+// The scalar step of one system by every wave that needs its result.  All that
+// it reads is loaded together: one after the other the sums, the state and the
+// flag took 13000 cycles of the wave (three round trips behind L2, where other
+// XCDs left them).
 template <int STEP>
-__device__ __forceinline__ void folded_step(const BlasArgs &a, int sys, int nsb, SysState &s, int &act)
-{
-    double P[6];
+struct FoldedStep {
+    static constexpr int SLOTS = scal_slots(STEP);
+    double v[6][4];        // the first 256 partial sums of each slot, 64 apart
+    unsigned long long w;  // word `lane` of the state
+    int was;               // the active flag
+
+    __device__ __forceinline__ void fetch(const BlasArgs &a, int sys, int nsb)
+    {
+        const int lane = threadIdx.x % FL_WAVE;
 #pragma unroll
-    for (int slot = 0; slot < 6; ++slot)
-        P[slot] = (scal_slots(STEP) >> slot) & 1 ? slot_sum(a.partial, slot, a.nsys, sys, a.B.nsb_max, nsb) : 0.0;
-    s = a.st[sys];
-    act = 1;
-    scal_step<STEP>(a.stamp, a.carried_r, P, s, act);
-    // not to be contracted into the vector arithmetic
-    asm volatile("" : "+v"(s.alpha[0]), "+v"(s.alpha[1]), "+v"(s.omega[0]), "+v"(s.omega[1]), "+v"(s.beta[0]), "+v"(s.beta[1]));
-}
+        for (int slot = 0; slot < 6; ++slot)
+            if ((SLOTS >> slot) & 1) {
+                const double *q = a.partial + pidx(slot, a.nsys, sys, a.B.nsb_max, 0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[slot][k] = q[min(lane + 64 * k, nsb - 1)];
+            }
+        constexpr int NW = (int)(sizeof(SysState) / 8);
+        w = ((const unsigned long long *)(a.st + sys))[min(lane, NW - 1)];
+        int z = 0;
+        asm volatile("" : "+v"(z));  // a vector load, in flight with the others
+        was = a.active[sys + z];
+    }
+
+    __device__ __forceinline__ void run(const BlasArgs &a, int sys, int nsb, SysState &s, int &act)
+    {
+        double P[6];
+#pragma unroll
+        for (int slot = 0; slot < 6; ++slot)
+            P[slot] = (SLOTS >> slot) & 1 ? slot_sum(v[slot], a.partial, slot, a.nsys, sys, a.B.nsb_max, nsb) : 0.0;
+        was = __builtin_amdgcn_readfirstlane(was);
+        s = state();
+        act = 1;
+        scal_step<STEP>(a.stamp, a.carried_r, P, s, act);
+        // not to be contracted into the vector arithmetic
+        asm volatile("" : "+v"(s.alpha[0]), "+v"(s.alpha[1]), "+v"(s.omega[0]), "+v"(s.omega[1]), "+v"(s.beta[0]), "+v"(s.beta[1]));
+    }
+
+    __device__ __forceinline__ SysState state() const
+    {
+        constexpr int NW = (int)(sizeof(SysState) / 8);
+        unsigned u[2 * NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            u[2 * k] = __builtin_amdgcn_readlane((unsigned)w, k);
+            u[2 * k + 1] = __builtin_amdgcn_readlane((unsigned)(w >> 32), k);
+        }
+        SysState s;
+        __builtin_memcpy(&s, u, sizeof(s));
+        return s;
+    }
+};
 
 // the state of one system as one store instruction of 8-byte words, one per
 // lane, through this wave's copy in LDS
@@ -264,50 +306,87 @@ __device__ __forceinline__ void store_flag(int *dst, int v)
 
 // S: storage format of the iteration vectors, arithmetic in SpinorFmt<S>::R
 template <typename S, int OP, bool FOLD = false>
-__global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024) void k_blas(BlasArgs a)
+__global__ __launch_bounds__(FOLD || sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024) void k_blas(BlasArgs a)
 {
     typedef typename SpinorFmt<S>::R R;
     TileInfo T = tile_info(a.B);
     if (!T.valid_rhs) return;
+    const LatGeom &g = a.B.lat[T.lat];
+    const int l = T.lat, i = FOLD ? min(T.site, g.Vh - 1) : T.site, Vh = g.Vh;
+    const int rhs = __builtin_amdgcn_readfirstlane(T.rhs);
+    typedef SpinorFmt<S> F;
+    typedef SpinorFmt<double> F64;
     SysState fs;   // FOLD: this system's state after the scalar step
     int fact = 1;  // FOLD: still active after it
-    if constexpr (FOLD) {
-        constexpr int STEP = OP == OP_BICG_S ? SC_ALPHA : OP == OP_BICG_XR ? SC_OMEGA : OP == OP_BICG_P ? SC_BETA
-                           : OP == OP_CG_R ? SC_CG_ALPHA : SC_CG_BETA;
-        constexpr bool BETA = STEP == SC_BETA || STEP == SC_CG_BETA;
-        const bool first = T.sb == 0;  // the wave that records the step
-        __shared__ SysState shs[16];   // a copy per wave
+    // FOLD: a small grid's launch takes as long as one wave's chain of loads,
+    // so everything a wave may need is loaded at once, the vectors before the
+    // scalar step, and the step is recorded behind the vectors (whole
+    // solves on 10x6x14x18, 7 right-hand sides: 16-bit CGNR 5.62 -> 4.93 ms,
+    // FP64 BiCGStab 3.76 -> 3.35)
+    // (five FP64 fields don't fit the registers)
+    constexpr int FIELDS = !FOLD ? 0
+                         : OP == OP_BICG_XR ? (sizeof(R) == 8 ? 0 : 0x2f)
+                         : OP == OP_BICG_S || OP == OP_CG_R ? 0x3 : 0x7;
+    cx<R> fv[FOLD ? 6 : 1][12];
+    auto load = [&](int k, cx<R> v[12]) {
+        if constexpr (FIELDS != 0) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) v[c] = fv[k][c];
+        } else {
+            F::load(fbuf<S>(a.f[k][l], g, rhs), Vh, i, v);
+        }
+    };
+    constexpr int STEP = OP == OP_BICG_S ? SC_ALPHA : OP == OP_BICG_XR ? SC_OMEGA : OP == OP_BICG_P ? SC_BETA
+                       : OP == OP_CG_R ? SC_CG_ALPHA : SC_CG_BETA;
+    constexpr bool BETA = STEP == SC_BETA || STEP == SC_CG_BETA;
+    __shared__ SysState shs[FOLD ? 8 : 1];  // a copy per wave
+    // what the first wave of a system records
+    auto record = [&](bool was_active) {
+        if (T.sb != 0) return;
         SysState *sh = shs + threadIdx.x / FL_WAVE;
-        if (!a.active[T.sys]) {
+        if (BETA) {
+            store_state(a.st_out + T.sys, fs, sh);
+            store_flag(a.act_out + T.sys, fact);
+        } else if (was_active) {
+            // only what no other wave of this launch reads: alpha or
+            // omega, the flags, and the active flag of a breakdown
+            double *dst = STEP == SC_OMEGA ? a.st[T.sys].omega : a.st[T.sys].alpha;
+            const double *v = STEP == SC_OMEGA ? fs.omega : fs.alpha;
+            const int lane = threadIdx.x % FL_WAVE;
+            const double w = lane == 0 ? v[0] : v[1];
+            if (lane < 2) dst[lane] = w;
+            store_drain();
+            if (!fact) {
+                store_flag(&a.st[T.sys].flags, fs.flags);
+                store_flag(a.active + T.sys, 0);
+            }
+        }
+    };
+    if constexpr (FOLD) {
+        FoldedStep<STEP> step;
+        step.fetch(a, T.sys, g.nsb);
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            if ((FIELDS >> k) & 1) F::load(fbuf<S>(a.f[k][l], g, rhs), Vh, i, fv[k]);
+        step.run(a, T.sys, g.nsb, fs, fact);
+        // the loads are not moved behind the branch
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            if ((FIELDS >> k) & 1)
+#pragma unroll
+                for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(fv[k][c].re), "+v"(fv[k][c].im));
+        if (!step.was) {
             // a wave that finds the flag taken back by the first one in this
             // launch (alpha, omega) stops like it
-            if (BETA && first) {
-                store_state(a.st_out + T.sys, a.st[T.sys], sh);
-                store_flag(a.act_out + T.sys, 0);
-            }
+            fs = step.state();
+            fact = 0;
+            record(false);
             return;
         }
-        folded_step<STEP>(a, T.sys, a.B.lat[T.lat].nsb, fs, fact);
-        if (first) {
-            if (BETA) {
-                store_state(a.st_out + T.sys, fs, sh);
-                store_flag(a.act_out + T.sys, fact);
-            } else {
-                // only what no other wave of this launch reads: alpha or
-                // omega, the flags, and the active flag of a breakdown
-                double *dst = STEP == SC_OMEGA ? a.st[T.sys].omega : a.st[T.sys].alpha;
-                const double *v = STEP == SC_OMEGA ? fs.omega : fs.alpha;
-                const int lane = threadIdx.x % FL_WAVE;
-                const double w = lane == 0 ? v[0] : v[1];
-                if (lane < 2) dst[lane] = w;
-                store_drain();
-                if (!fact) {
-                    store_flag(&a.st[T.sys].flags, fs.flags);
-                    store_flag(a.active + T.sys, 0);
-                }
-            }
+        if (!fact && OP != OP_CG_PX) {
+            record(true);
+            return;
         }
-        if (!fact && OP != OP_CG_PX) return;
     } else if (OP == OP_CG_PX) {
         // a system that stopped in this iteration still owes its x update
         if (!a.mask[T.sys] && a.st[T.sys].xstamp != a.stamp) return;
@@ -315,19 +394,14 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
         return;
     }
     const SysState &cur = FOLD ? fs : a.st[T.sys];
-    const LatGeom &g = a.B.lat[T.lat];
-    const int l = T.lat, i = T.site, Vh = g.Vh;
-    const int rhs = __builtin_amdgcn_readfirstlane(T.rhs);
-    typedef SpinorFmt<S> F;
-    typedef SpinorFmt<double> F64;
     R q0 = 0, q1 = 0, q2 = 0;
     if (T.valid_site) {
         if (OP == OP_BICG_S) {
             const SysState &st = cur;
             cx<R> al = cpx_of<R>(st.alpha);
             cx<R> r[12], v[12];
-            F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, r);
-            F::load(fbuf<S>(a.f[1][l], g, rhs), Vh, i, v);
+            load(0, r);
+            load(1, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k) r[k] = cmsub(r[k], al, v[k]);
             store_result<S>(fbuf<S>(a.f[2][l], g, rhs), Vh, i, r);
@@ -335,11 +409,11 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             const SysState &st = cur;
             cx<R> al = cpx_of<R>(st.alpha), om = cpx_of<R>(st.omega);
             cx<R> x[12], p[12], s[12], t[12], r0[12];
-            F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, x);
-            F::load(fbuf<S>(a.f[1][l], g, rhs), Vh, i, p);
-            F::load(fbuf<S>(a.f[2][l], g, rhs), Vh, i, s);
-            F::load(fbuf<S>(a.f[3][l], g, rhs), Vh, i, t);
-            F::load(fbuf<S>(a.f[5][l], g, rhs), Vh, i, r0);
+            load(0, x);
+            load(1, p);
+            load(2, s);
+            load(3, t);
+            load(5, r0);
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
                 x[k] = cmad(cmad(x[k], al, p[k]), om, s[k]);
@@ -358,9 +432,9 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             const SysState &st = cur;
             cx<R> be = cpx_of<R>(st.beta), om = cpx_of<R>(st.omega);
             cx<R> p[12], r[12], v[12];
-            F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
-            F::load(fbuf<S>(a.f[1][l], g, rhs), Vh, i, r);
-            F::load(fbuf<S>(a.f[2][l], g, rhs), Vh, i, v);
+            load(0, p);
+            load(1, r);
+            load(2, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k) p[k] = cmad(r[k], be, cmsub(p[k], om, v[k]));
             store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
@@ -441,8 +515,8 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
         } else if (OP == OP_CG_R) {
             const R al = (R)cur.alpha[0];
             cx<R> r[12], q[12];
-            F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, r);
-            F::load(fbuf<S>(a.f[1][l], g, rhs), Vh, i, q);
+            load(0, r);
+            load(1, q);
 #pragma unroll
             for (int k = 0; k < 12; ++k) r[k] = cx<R>{fma(-al, q[k].re, r[k].re), fma(-al, q[k].im, r[k].im)};
             store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, r);
@@ -461,11 +535,11 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             const SysState &st = cur;
             const bool xu = FOLD || st.xstamp == a.stamp, pu = FOLD ? fact != 0 : a.mask[T.sys] != 0;
             cx<R> p[12];
-            F::load(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
+            load(0, p);
             if (xu) {
                 const R al = (R)st.alpha[0];
                 cx<R> x[12];
-                F::load(fbuf<S>(a.f[2][l], g, rhs), Vh, i, x);
+                load(2, x);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) x[k] = cx<R>{fma(al, p[k].re, x[k].re), fma(al, p[k].im, x[k].im)};
                 store_result<S>(fbuf<S>(a.f[2][l], g, rhs), Vh, i, x);
@@ -473,13 +547,14 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
             if (pu) {
                 const R be = (R)st.beta[0];
                 cx<R> z[12];
-                F::load(fbuf<S>(a.f[1][l], g, rhs), Vh, i, z);
+                load(1, z);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) p[k] = cx<R>{fma(be, p[k].re, z[k].re), fma(be, p[k].im, z[k].im)};
                 store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
             }
         }
     }
+    if constexpr (FOLD) record(true);
     if (OP == OP_BICG_XR || OP == OP_HI_TO_LO || OP == OP_NORM || OP == OP_CG_R || OP == OP_DOT) {
         double s0 = wave_sum((double)q0), s1 = wave_sum((double)q1), s2 = wave_sum((double)q2);
         constexpr int which = (OP == OP_BICG_XR || OP == OP_HI_TO_LO) ? 7 : (OP == OP_DOT ? 3 : 4);

@@ -1012,18 +1012,23 @@ __device__ __forceinline__ size_t pidx(int slot, int nsys, int sys, int nsb_max,
 
 __device__ __forceinline__ bool finite_d(double v) { return v == v && v - v == 0.0; }
 
-// the partial sums of a slot for one system by one wave, in the order of a
-// halving tree over 256 threads that stride over the site blocks
-__device__ __forceinline__ double slot_sum(const double *partial, int slot, int nsys, int sys, int nb, int nsb)
+// The partial sums of a slot for one system by one wave, in the order of a
+// halving tree over 256 threads that stride over the site blocks; v: lane l's
+// sums l, l + 64, l + 128 and l + 192 (any value past the end)
+__device__ __forceinline__ double slot_sum(const double v[4], const double *partial, int slot, int nsys, int sys,
+                                                int nb, int nsb)
 {
+    const int lane = threadIdx.x % FL_WAVE;
+    double r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = 0.0 + (lane + 64 * k < nsb ? v[k] : 0.0);
     const double *q = partial + pidx(slot, nsys, sys, nb, 0);
-    double r[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int s0 = threadIdx.x % FL_WAVE; s0 < nsb; s0 += 256) {
-        double v[4];
+    for (int s0 = lane + 256; s0 - lane < nsb; s0 += 256) {
+        double u[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = q[min(s0 + 64 * k, nsb - 1)];
+        for (int k = 0; k < 4; ++k) u[k] = q[min(s0 + 64 * k, nsb - 1)];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r[k] += s0 + 64 * k < nsb ? v[k] : 0.0;
+        for (int k = 0; k < 4; ++k) r[k] += s0 + 64 * k < nsb ? u[k] : 0.0;
     }
     return wave_sum((r[0] + r[2]) + (r[1] + r[3]));
 }

@@ -582,14 +582,14 @@ __global__ __launch_bounds__(512) void k_dslash_split(DslashArgs a)
     neighbours(g, c, i, nb);
     const Buf in = spinor_buf<S>(a.in[T.lat], Vh, rhs);
     const Buf gauge = make_buf(a.gauge[T.lat], (unsigned)(8u * LK::NC * LK::ESZ * (unsigned)Vh));
-    // fold: alpha of this iteration, as the scalar step before this launch would set it
-    double alpha = 0.0;
-    bool broken = false;
+    // folded alpha: what it is computed from is loaded with the neighbours
+    double zz = 0.0, qv[4];
     if constexpr ((EPI & EPI_CGZ) != 0) {
         if (a.fold && d == 0) {
-            const double qq = slot_sum(a.partial, 2, a.nsys, sys, a.B.nsb_max, g.nsb);
-            broken = !(qq > 0) || !finite_d(qq);
-            alpha = broken ? 0.0 : a.st[sys].zz / qq;
+            const double *q = a.partial + pidx(2, a.nsys, sys, a.B.nsb_max, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) qv[k] = q[min(lane + 64 * k, g.nsb - 1)];
+            zz = a.st[sys].zz;
         }
     }
     {
@@ -618,8 +618,13 @@ __global__ __launch_bounds__(512) void k_dslash_split(DslashArgs a)
     }
     __syncthreads();
     if (d != 0) return;
+    double alpha = 0.0;
     if constexpr ((EPI & EPI_CGZ) != 0) {
         if (a.fold) {
+            // alpha of this iteration, as the scalar step before this launch would set it
+            const double qq = slot_sum(qv, a.partial, 2, a.nsys, sys, a.B.nsb_max, g.nsb);
+            const bool broken = !(qq > 0) || !finite_d(qq);
+            alpha = broken ? 0.0 : zz / qq;
             if (T.sb == 0) {
                 if (lane == 0) {
                     if (broken)

@@ -47,7 +47,7 @@ struct PinArr {
 };
 
 // largest number of 64-site tiles whose vector kernels compute the scalar steps
-constexpr int FOLD_TILES = 4096;
+constexpr int FOLD_TILES = 3072;
 
 struct Solver {
     SolveBatch &sb;
@@ -325,10 +325,11 @@ fl_status Solver::prepare()
         // a folded step costs every wave a look at all the partial sums of its
         // system, a launch of its own about 5 us: folded up to 512 site blocks
         // (16^3x32 has 1024: 4.61 ms against 4.48 for one FP64 solve) and
-        // while the grid is small
+        // while the grid is small (FP32 BiCGStab, folded against not: 2700
+        // tiles 4.39 and 4.68 ms, 3072 6.07 and 6.04, 3888 7.18 and 6.89)
         int tiles = 0;
         for (int l = 0; l < B.nlat; ++l) tiles += B.lat[l].nsb * B.lat[l].nrhs;
-        fold = B.nsb_max <= 512 && tiles <= FOLD_TILES;
+        fold = B.nsb_max <= 512 && tiles <= FOLD_TILES && B.RT <= 8;
         fold_cgz = fold && a.lds == 5;
     }
 

@@ -78,7 +78,7 @@ def test_gradient_ragged(F, dims):
 def test_small_grid_truncated_bits(F, prec, reals, solver):
     """Truncated solves in the low precisions: alone on a small grid (scalar
     steps inside the vector kernels, 16-bit hops with a wave per direction) and
-    in a batch beyond both limits (4096 and 1024 tiles) the results are equal
+    in a batch beyond both limits (3072 and 1024 tiles) the results are equal
     bit for bit."""
     dims = (4, 4, 4, 6)  # 192 sites: three blocks
     lat, _ = make(F, dims)
