@@ -26,6 +26,14 @@ __device__ __forceinline__ Buf fbuf(const void *base, const LatGeom &g, int rhs)
     return spinor_buf<S>(base, g.Vh, rhs);
 }
 
+// a result that the next kernel reads as neighbours (p, s): kept in the caches
+// (FP32, 16^3x32, 12 right-hand sides: solve 79.0 -> 77.9 ms)
+template <typename S>
+__device__ __forceinline__ void store_next(const Buf &b, int Vh, int i, cx<typename SpinorFmt<S>::R> s[12])
+{
+    SpinorFmt<S>::template store<0>(b, Vh, i, s);
+}
+
 template <typename R>
 __device__ __forceinline__ cx<R> cpx_of(const double *v)
 {
@@ -305,7 +313,8 @@ __device__ __forceinline__ void store_flag(int *dst, int v)
 }
 
 // S: storage format of the iteration vectors, arithmetic in SpinorFmt<S>::R
-template <typename S, int OP, bool FOLD = false>
+// LARGE: OP_CG_PX on fields beyond the caches.
+template <typename S, int OP, bool FOLD = false, bool LARGE = false>
 __global__ __launch_bounds__(FOLD || sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024) void k_blas(BlasArgs a)
 {
     typedef typename SpinorFmt<S>::R R;
@@ -328,10 +337,19 @@ __global__ __launch_bounds__(FOLD || sizeof(typename SpinorFmt<S>::R) == 8 ? 512
                          : OP == OP_BICG_XR ? (sizeof(R) == 8 ? 0 : 0x2f)
                          : OP == OP_BICG_S || OP == OP_CG_R ? 0x3 : 0x7;
     cx<R> fv[FOLD ? 6 : 1][12];
+    // fields that the next kernels don't read, loaded so that the others stay
+    // cached: BiCGStab's r of s, x, s, t, r0 of the x and r update, v of p
+    // (16^3x32, FP32, 12 right-hand sides: solve 81.8 -> 79.0 ms, FP64, 8: 21.9 ->
+    // 21.1); CGNR's z and x
+    // where they are too large for the cache anyway (LARGE)
+    constexpr unsigned ONCE = OP == OP_BICG_S ? 0x1 : OP == OP_BICG_XR ? 0x2d : OP == OP_BICG_P ? 0x4
+                            : OP == OP_CG_PX && LARGE ? 0x6 : 0;
     auto load = [&](int k, cx<R> v[12]) {
         if constexpr (FIELDS != 0) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) v[c] = fv[k][c];
+        } else if ((ONCE >> k) & 1) {
+            load_once<S, R>(fbuf<S>(a.f[k][l], g, rhs), Vh, i, v);
         } else {
             F::load(fbuf<S>(a.f[k][l], g, rhs), Vh, i, v);
         }
@@ -404,7 +422,7 @@ __global__ __launch_bounds__(FOLD || sizeof(typename SpinorFmt<S>::R) == 8 ? 512
             load(1, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k) r[k] = cmsub(r[k], al, v[k]);
-            store_result<S>(fbuf<S>(a.f[2][l], g, rhs), Vh, i, r);
+            store_next<S>(fbuf<S>(a.f[2][l], g, rhs), Vh, i, r);
         } else if (OP == OP_BICG_XR) {
             const SysState &st = cur;
             cx<R> al = cpx_of<R>(st.alpha), om = cpx_of<R>(st.omega);
@@ -437,7 +455,7 @@ __global__ __launch_bounds__(FOLD || sizeof(typename SpinorFmt<S>::R) == 8 ? 512
             load(2, v);
 #pragma unroll
             for (int k = 0; k < 12; ++k) p[k] = cmad(r[k], be, cmsub(p[k], om, v[k]));
-            store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
+            store_next<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
         } else if (OP == OP_HI_TO_LO) {
             cx<double> h[12];
             cx<R> lo[12], r0[12];
@@ -550,7 +568,7 @@ __global__ __launch_bounds__(FOLD || sizeof(typename SpinorFmt<S>::R) == 8 ? 512
                 load(1, z);
 #pragma unroll
                 for (int k = 0; k < 12; ++k) p[k] = cx<R>{fma(be, p[k].re, z[k].re), fma(be, p[k].im, z[k].im)};
-                store_result<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
+                store_next<S>(fbuf<S>(a.f[0][l], g, rhs), Vh, i, p);
             }
         }
     }
@@ -576,6 +594,13 @@ void dispatch(const BlasArgs &a, dim3 grid, dim3 block, hipStream_t s)
         }
         return;
     }
+    // OP_CG_PX: its three fields against the 256 MB of the Infinity Cache.  z and
+    // x non-temporally: 490 MB (16-bit, 8^3x16, 768 right-hand sides) 814 -> 795
+    // ms a timeslice, 450 MB (FP32, 16^3x32, 24) 56.8 -> 55.7 ms; 143 MB (FP32,
+    // 12^3x24, 24) 18.0 -> 18.3, 245 MB (16-bit, 16^3x32, 24) 42.8 -> 43.0
+    size_t px = 0;
+    for (int l = 0; l < a.B.nlat; ++l) px += 3 * (size_t)SpinorFmt<S>::SITE_BYTES * a.B.lat[l].Vh * a.B.lat[l].nrhs;
+    const bool large = px > (size_t)256 << 20;
     switch (a.op) {
     case OP_BICG_S: hipLaunchKernelGGL((k_blas<S, OP_BICG_S>), grid, block, 0, s, a); break;
     case OP_BICG_XR: hipLaunchKernelGGL((k_blas<S, OP_BICG_XR>), grid, block, 0, s, a); break;
@@ -587,7 +612,12 @@ void dispatch(const BlasArgs &a, dim3 grid, dim3 block, hipStream_t s)
     case OP_ZERO: hipLaunchKernelGGL((k_blas<S, OP_ZERO>), grid, block, 0, s, a); break;
     case OP_CG_R: hipLaunchKernelGGL((k_blas<S, OP_CG_R>), grid, block, 0, s, a); break;
     case OP_CG_P: hipLaunchKernelGGL((k_blas<S, OP_CG_P>), grid, block, 0, s, a); break;
-    case OP_CG_PX: hipLaunchKernelGGL((k_blas<S, OP_CG_PX>), grid, block, 0, s, a); break;
+    case OP_CG_PX:
+        if (large)
+            hipLaunchKernelGGL((k_blas<S, OP_CG_PX, false, true>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((k_blas<S, OP_CG_PX>), grid, block, 0, s, a);
+        break;
     case OP_DOT: hipLaunchKernelGGL((k_blas<S, OP_DOT>), grid, block, 0, s, a); break;
     case OP_CG_FIXP: hipLaunchKernelGGL((k_blas<S, OP_CG_FIXP>), grid, block, 0, s, a); break;
     default: launch_unsupported("vector operation"); break;

@@ -558,6 +558,36 @@ __device__ __forceinline__ void store_result(const Buf &b, int Vh, int i, cx<typ
     SpinorFmt<S>::template store<ST_STREAM>(b, Vh, i, s);
 }
 
+// a site of a field that no later kernel reads soon, loaded non-temporally
+template <typename S, typename R>
+__device__ __forceinline__ void load_once(const Buf &b, int Vh, int i, cx<R> s[12])
+{
+    if constexpr (std::is_same<S, H16>::value) {
+        v4f v[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b128(b.r, i * 16, c * Vh * 16, LD_STREAM);
+        const float sc =
+            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b.r, i * 4, 3 * Vh * 16, LD_STREAM));
+        SpinorFmt<H16>::unpack(v, s);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) s[k] = cx<float>{s[k].re * sc, s[k].im * sc};
+    } else if constexpr (std::is_same<S, float>::value) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            const v4f v = __builtin_amdgcn_raw_buffer_load_b128(b.r, i * 16, c * Vh * 16, LD_STREAM);
+            s[2 * c] = cx<float>{v.x, v.y};
+            s[2 * c + 1] = cx<float>{v.z, v.w};
+        }
+    } else {
+        static_assert(std::is_same<S, double>::value, "spinor format");
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const double2 d = v4f_to_d2(__builtin_amdgcn_raw_buffer_load_b128(b.r, i * 16, c * Vh * 16, LD_STREAM));
+            s[c] = cx<double>{d.x, d.y};
+        }
+    }
+}
+
 // per-wave buffer view of right-hand side `rhs` of a field in format S
 template <typename S>
 __device__ __forceinline__ Buf spinor_buf(const void *base, int Vh, int rhs)

@@ -27,43 +27,25 @@
 
 namespace {
 
-// An own-site operand of the epilogue (x, y): read once by this kernel, so
-// 16-bit and FP32 fields are loaded non-temporally and leave L2 to the
-// neighbour spinors that other workgroups still read (the dagger hop that
-// updates z, which reads two such fields, at 16^3x32 with 384 right-hand
-// sides: 1235 instead of 1276 us per launch with 16-bit fields, 2223
-// instead of 2358 us with FP32 fields)
-template <typename S, typename R>
-__device__ __forceinline__ void load_once(const Buf &b, int Vh, int i, cx<R> s[12])
-{
-    if constexpr (std::is_same<S, H16>::value) {
-        v4f v[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) v[c] = __builtin_amdgcn_raw_buffer_load_b128(b.r, i * 16, c * Vh * 16, LD_STREAM);
-        const float sc =
-            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b.r, i * 4, 3 * Vh * 16, LD_STREAM));
-        SpinorFmt<H16>::unpack(v, s);
-#pragma unroll
-        for (int k = 0; k < 12; ++k) s[k] = cx<float>{s[k].re * sc, s[k].im * sc};
-    } else if constexpr (std::is_same<S, float>::value) {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            const v4f v = __builtin_amdgcn_raw_buffer_load_b128(b.r, i * 16, c * Vh * 16, LD_STREAM);
-            s[2 * c] = cx<float>{v.x, v.y};
-            s[2 * c + 1] = cx<float>{v.z, v.w};
-        }
-    } else {
-        SpinorFmt<S>::load(b, Vh, i, s);
-    }
-}
-
+// The epilogue's own-site operands (x, y) are read once by the kernel: load_once
+// leaves L2 to the neighbour spinors that other workgroups still read (the
+// dagger hop that updates z, which reads two such fields, at 16^3x32 with 384
+// right-hand sides: 1235 instead of 1276 us per launch with 16-bit fields, 2223
+// instead of 2358 us with FP32 fields).
 // S: storage format of the fields (SpinorFmt<S>), arithmetic in SpinorFmt<S>::R.
 // The reductions use the values as stored (after any rounding of the format).
-template <typename S, int EPI, typename R>
+// SMALL: a grid whose fields stay in the caches.
+template <typename S, int EPI, typename R, bool SMALL = false>
 __device__ __forceinline__ void epilogue(const DslashArgs &a, const TileInfo &T, const LatGeom &g, int rhs,
                                          const cx<R> acc[12], R &q0, R &q1, R &q2, double alpha = 0.0)
 {
     typedef SpinorFmt<S> F;
+    auto own = [&](const void *f, cx<R> v[12]) {
+        if constexpr (SMALL)
+            F::load(spinor_buf<S>(f, g.Vh, rhs), g.Vh, T.site, v);
+        else
+            load_once<S, R>(spinor_buf<S>(f, g.Vh, rhs), g.Vh, T.site, v);
+    };
     const R cb = (R)a.cb[T.lat];
     if constexpr (std::is_same<S, H16>::value && !(EPI & (EPI_XPAY | EPI_DOTX_NORM | EPI_DOTY))) {
         // 16-bit result cb * acc: cb enters the site scale, not the values
@@ -75,7 +57,7 @@ __device__ __forceinline__ void epilogue(const DslashArgs &a, const TileInfo &T,
     }
     cx<R> out[12], xv[12];
     if (EPI & EPI_XPAY) {
-        load_once<S, R>(spinor_buf<S>(a.x[T.lat], g.Vh, rhs), g.Vh, T.site, xv);
+        own(a.x[T.lat], xv);
         const R ca = (R)a.ca[T.lat];
         if (ca == (R)1) {
 #pragma unroll
@@ -91,7 +73,7 @@ __device__ __forceinline__ void epilogue(const DslashArgs &a, const TileInfo &T,
     if constexpr ((EPI & EPI_CGZ) != 0) {
         // out = y - alpha (x + cb acc), y the field this launch overwrites (own site only)
         cx<R> yv[12];
-        load_once<S, R>(spinor_buf<S>(a.y[T.lat], g.Vh, rhs), g.Vh, T.site, yv);
+        own(a.y[T.lat], yv);
         const R al = (R)(a.fold ? alpha : a.st[T.sys].alpha[0]);
 #pragma unroll
         for (int k = 0; k < 12; ++k) out[k] = cx<R>{fma(-al, out[k].re, yv[k].re), fma(-al, out[k].im, yv[k].im)};
@@ -139,7 +121,7 @@ __device__ __forceinline__ void epilogue(const DslashArgs &a, const TileInfo &T,
     }
     if (EPI & EPI_DOTY) {
         cx<R> yv[12];
-        load_once<S, R>(spinor_buf<S>(a.y[T.lat], g.Vh, rhs), g.Vh, T.site, yv);
+        own(a.y[T.lat], yv);
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
             cx<R> d = cjmul(yv[k], out[k]);
@@ -660,7 +642,7 @@ __global__ __launch_bounds__(512) void k_dslash_split(DslashArgs a)
         add(std::integral_constant<int, 5>());
         add(std::integral_constant<int, 6>());
         add(std::integral_constant<int, 7>());
-        epilogue<S, EPI>(a, T, g, rhs, acc, q0, q1, q2, alpha);
+        epilogue<S, EPI, R, true>(a, T, g, rhs, acc, q0, q1, q2, alpha);
     }
     reduce_partials<EPI>(a, T, q0, q1, q2);
 }
