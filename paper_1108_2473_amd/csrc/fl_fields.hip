@@ -359,7 +359,12 @@ __global__ void k_exact_contract(ExactContractArgs a)
 
 // one estimated site (t, xs) per thread, summing over the batch's sources
 // in order: acc[gamma] += sign * sum_{al, be, a} conj(eta_{al a}) Gamma_{al be} phi_{be a}
-__global__ void k_stoch_contract(StochContractArgs a)
+// Bound by its loads: per site the 16 spin sums over colour of eta^+ x phi are
+// accumulated over the right-hand sides in registers, the matrices applied once
+// at the end (with a matrix product per right-hand side and the sums of a
+// run-time number of matrices in scratch: a batch of an uneven truncated
+// estimate, 535 -> 341 us on 16^3x32 and 351 -> 123 us on 12^3x24).
+__global__ __launch_bounds__(128) void k_stoch_contract(StochContractArgs a)
 {
     const LatGeom &g = a.g;
     long long Vs = (long long)g.L[0] * g.L[1] * g.L[2];
@@ -373,36 +378,48 @@ __global__ void k_stoch_contract(StochContractArgs a)
     const size_t fs = (size_t)12 * g.Vh;
     const double2 *pf = ls.par ? a.po : a.pe;
     const double2 *nf = ls.par ? a.no : a.ne;
-    cx<double> acc[2][16];
-    for (int q = 0; q < 2; ++q)
-        for (int gi = 0; gi < a.ngamma; ++gi) acc[q][gi] = cx<double>{0, 0};
+    cx<double> acc[2][16];  // target, 4 al + be
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc[0][k] = acc[1][k] = cx<double>{0, 0};
     for (int j = 0; j < a.nrhs; ++j) {
         const int *job = a.job + JOB_INTS * j;
         if ((a.dil & FL_DIL_TIME) && job[JOB_T] != ls.t) continue;
-        const int tgt = job[JOB_TARGET] ? 1 : 0;
         const double sg = (double)job[JOB_SIGN];
         cx<double> eta[12], phi[12];
         SpinorFmt<double>::load(nf + j * fs, g.Vh, ls.cb, eta);
         SpinorFmt<double>::load(pf + j * fs, g.Vh, ls.cb, phi);
-        for (int gi = 0; gi < a.ngamma; ++gi) {
-            const double *G = a.gam + gi * 32;
-            cx<double> v{0, 0};
+#pragma unroll
+        for (int c = 0; c < 12; ++c) eta[c] = sg * eta[c];
+        auto add = [&](cx<double> *t) {
+#pragma unroll
             for (int al = 0; al < 4; ++al)
-                for (int be = 0; be < 4; ++be) {
-                    cx<double> gab{G[2 * (4 * al + be)], G[2 * (4 * al + be) + 1]};
-                    if (gab.re == 0 && gab.im == 0) continue;
-                    for (int c = 0; c < 3; ++c) v = v + cjmul(eta[3 * al + c], gab * phi[3 * be + c]);
-                }
-            acc[tgt][gi] = acc[tgt][gi] + sg * v;
-        }
+#pragma unroll
+                for (int be = 0; be < 4; ++be)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        t[4 * al + be] = cjmad(t[4 * al + be], eta[3 * al + c], phi[3 * be + c]);
+        };
+        if (job[JOB_TARGET])
+            add(acc[1]);
+        else
+            add(acc[0]);
     }
+#pragma unroll
     for (int q = 0; q < 2; ++q) {
         double2 *base = q ? a.acc1 : a.acc0;
         if (!base) continue;
         for (int gi = 0; gi < a.ngamma; ++gi) {
+            const double *G = a.gam + gi * 32;
+            cx<double> v{0, 0};
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const cx<double> gab{G[2 * k], G[2 * k + 1]};
+                if (gab.re == 0 && gab.im == 0) continue;
+                v = v + gab * acc[q][k];
+            }
             double2 *o = base + (gi * nt + tt) * Vs + xs;
             double2 cur = *o;
-            *o = make_double2(cur.x + acc[q][gi].re, cur.y + acc[q][gi].im);
+            *o = make_double2(cur.x + v.re, cur.y + v.im);
             store_drain();  // one store per gamma (their number is a run-time value)
         }
     }
