@@ -323,7 +323,9 @@ fl_status fl_bench_dslash(fl_ctx *ctx, int prec, int gauge_reals, int nrhs, int 
  * windows (for FL_PREC_H16 the packed hop of 3, every neighbour spinor
  * loaded two directions before its use), -1 the built-in choice (4; 1 for
  * FP64 workgroups of fewer than 4 right-hand sides; falling back to a
- * smaller mode when its LDS does not fit).  rt = 0 restores the built-in workgroup size.
+ * smaller mode when its LDS does not fit; with rt = 0, on grids of few site
+ * blocks, a workgroup per 64 sites of one right-hand side with a wavefront
+ * per direction).  rt = 0 restores the built-in workgroup size.
  * FL_ERR_ARG for out-of-range values or lds 3 with another precision. */
 fl_status fl_set_tile(fl_ctx *ctx, int prec, int gauge_reals, int rt, int group, int lds);
 
