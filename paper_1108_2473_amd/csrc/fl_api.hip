@@ -11,7 +11,7 @@
 #include "fl_host.h"
 
 void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *in, void *out, const void *x,
-                  double ca, double cb, bool dag, int epi, bool split_ok)
+                  double ca, double cb, bool dag, int epi)
 {
     int RT, G;
     tile_shape(c, LINK_F64_R18, nrhs, &RT, &G);
@@ -29,7 +29,7 @@ void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *i
     a.ca[0] = ca;
     a.cb[0] = cb;
     if (epi < 0) epi = x ? EPI_XPAY : EPI_PLAIN;
-    dslash_config(c, LINK_F64_R18, a, split_ok);
+    dslash_config(c, LINK_F64_R18, a, true);
     launch_dslash(LINK_F64_R18, a, dag, epi, c->stream);
 }
 
@@ -138,9 +138,9 @@ fl_status check_params(fl_ctx *c, const fl_solver_params *p)
 
 // single-lattice hopping launch on FP64 fields
 void hop64(fl_ctx *c, int nrhs, int par, const void *in, void *out, const void *x, double ca, double cb, bool dag,
-           bool same_bits = false)
+           int epi = -1)
 {
-    hop64_launch(c, links(c, LINK_F64_R18), nrhs, par, in, out, x, ca, cb, dag, -1, !same_bits);
+    hop64_launch(c, links(c, LINK_F64_R18), nrhs, par, in, out, x, ca, cb, dag, epi);
 }
 
 // |f|^2 per right-hand side of FP64 (even, odd) fields, summed on the host in
@@ -439,8 +439,8 @@ void dslash_config(const fl_ctx *c, LinkFormat fmt, DslashArgs &a, bool split_ok
             tiles += a.B.lat[l].nsb * a.B.lat[l].nrhs;
             few &= a.B.lat[l].nrhs < 4;
         }
-        // the FP64 and FP32 results round differently from the other kernels'
-        // (which FP64 workgroups of fewer than 4 right-hand sides do in any case)
+        // FP64 and FP32: up to 3 right-hand sides; more share a workgroup's
+        // staged links
         if (tiles <= split_tiles(fmt) && (few || fmt == LINK_Q16_R12)) {
             // a workgroup per 64 sites of one right-hand side
             a.lds = 5;
@@ -763,7 +763,6 @@ fl_status fl_apply_schur(fl_ctx *c, const double *in, double *out, int nrhs, int
         sb.bh[0] = (const double2 *)be;
         sb.xh[0] = (double2 *)xe;
         sb.bnorm.assign(n, 1.0);
-        sb.same_bits = true;
         if ((e = schur_apply_batch(sb, *p, dagger != 0))) return e;
         if ((e = hip_check(c, hipMemsetAsync(xo, 0, fb, c->stream), "memset"))) return e;
         launch_eo_to_canon((double2 *)xe, (double2 *)xo, cout, g, n, c->stream);
@@ -811,7 +810,7 @@ fl_status fl_solve(fl_ctx *c, const double *b, double *x, int nrhs, const fl_sol
         std::vector<double> b2;
         if ((e = norms64(c, n, be, bo, b2))) return e;
         // bhat_e = b_e + k H_eo b_o
-        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false, p->truncated != 0);
+        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false);
         SolveBatch sb;
         sb.nlat = 1;
         sb.ctx[0] = c;
@@ -824,7 +823,7 @@ fl_status fl_solve(fl_ctx *c, const double *b, double *x, int nrhs, const fl_sol
         fl_status se = solve_schur_batch(sb, *p, res);
         if (se != FL_OK && se != FL_ERR_NOCONV && se != FL_ERR_BREAKDOWN) return se;
         // x_o = b_o + k H_oe x_e
-        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false, p->truncated != 0);
+        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false);
         // stopping rule on the full operator: r = b - D x
         std::vector<double> r2;
         if ((e = full_residual2(c, n, be, bo, xe, xo, r2))) return e;
@@ -891,7 +890,7 @@ fl_status fl_loops_exact_sites(fl_ctx *c, const long long *sites, long long nsit
         if ((e = hip_check(c, hipMemsetAsync(be, 0, fb, c->stream), "memset"))) return e;
         if ((e = hip_check(c, hipMemsetAsync(bo, 0, fb, c->stream), "memset"))) return e;
         launch_point_sources((double2 *)be, (double2 *)bo, dsites + s0, ns, g, c->stream);
-        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false, p->truncated != 0);
+        hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false);
         SolveBatch sb;
         sb.nlat = 1;
         sb.ctx[0] = c;
@@ -903,7 +902,7 @@ fl_status fl_loops_exact_sites(fl_ctx *c, const long long *sites, long long nsit
         fl_status se = solve_schur_batch(sb, *p, res);
         if (se != FL_OK && se != FL_ERR_NOCONV && se != FL_ERR_BREAKDOWN) return se;
         // acceptance on the full operator (point sources: |b| = 1)
-        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false, p->truncated != 0);  // x_o = b_o + k H_oe x_e
+        hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false);  // x_o = b_o + k H_oe x_e
         std::vector<double> r2;
         if ((e = full_residual2(c, n, be, bo, xe, xo, r2))) return e;
         const double secs = now_s() - t_batch;
@@ -1077,8 +1076,7 @@ fl_status fl_loops_stochastic_multi(fl_ctx **ctxs, int nctx, const fl_noise_para
             const double t_batch = now_s();
             // every lattice takes part in the batch (possibly with no rhs)
             SolveBatch sb;
-            sb.same_bits = true;
-            sb.nlat = 0;
+                sb.nlat = 0;
             std::vector<int> lat_of;
             for (int l = 0; l < nctx; ++l) {
                 sb.ctx[sb.nlat] = ctxs[l];
@@ -1117,7 +1115,7 @@ fl_status fl_loops_stochastic_multi(fl_ctx **ctxs, int nctx, const fl_noise_para
                 LatGeom g = lat_geom(c, n);
                 launch_noise_sources((double2 *)be, (double2 *)bo, nbt, g, st);
                 if ((e = norms64(c, n, be, bo, bn[l]))) return e;
-                hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false, true);
+                hop64(c, n, 0, bo, bh, be, 1.0, c->kappa, false);
             }
             for (int l = 0; l < nctx; ++l)
                 for (int k = 0; k < nr[l]; ++k) sb.bnorm.push_back(std::sqrt(bn[l][k]));
@@ -1133,7 +1131,7 @@ fl_status fl_loops_stochastic_multi(fl_ctx **ctxs, int nctx, const fl_noise_para
                 void *be = c->pool[WS_BE].p, *bo = c->pool[WS_BO].p, *xe = c->pool[WS_XE].p;
                 void *xo = ws_get(c, WS_XO, fb);
                 if (!xo) return set_err(c, FL_ERR_NOMEM, "device allocation failed");
-                hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false, true);  // x_o = eta_o + k H_oe x_e
+                hop64(c, n, 1, xe, xo, bo, 1.0, c->kappa, false);  // x_o = eta_o + k H_oe x_e
                 // statistics; solves that are not truncated are accepted on the
                 // full operator
                 std::vector<double> r2;

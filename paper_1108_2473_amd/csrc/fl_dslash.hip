@@ -494,8 +494,7 @@ __global__ __launch_bounds__(sizeof(typename SpinorFmt<S>::R) == 8 ? 512 : 1024)
 // in the order of hop_site and runs the epilogue.  With fewer tiles than the
 // chip holds waves the hop's time is one wave's chain of loads: eight round
 // trips become one (16-bit, 8^3x16, one right-hand side: a whole CGNR solve
-// 4.69 -> 3.51 ms).  16-bit results equal the other kernels' bit for bit; in
-// FP64 and FP32 those contract the sum into the products, which can't be done here.
+// 4.69 -> 3.51 ms).  The results equal the other kernels' bit for bit.
 // ---------------------------------------------------------------------------
 template <typename S, class LK>
 struct SplitHop {

@@ -324,10 +324,9 @@ BatchGeom batch_geom(fl_ctx *const *ctx, const int *nrhs, int nlat, int RT, int 
 // right-hand-side blocks per site sweep (the autotuner's choice if any)
 void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G);
 // single-lattice hopping launch on FP64 fields with the given FP64 links:
-// out = ca x + cb H in (x may be null: out = cb H in); epi < 0: XPAY if x;
-// split_ok as in dslash_config
+// out = ca x + cb H in (x may be null: out = cb H in); epi < 0: XPAY if x
 void hop64_launch(fl_ctx *c, const void *gauge, int nrhs, int par, const void *in, void *out, const void *x,
-                  double ca, double cb, bool dag, int epi = -1, bool split_ok = true);
+                  double ca, double cb, bool dag, int epi = -1);
 // out = (1 - kappa H) in on canonical FP64 fields that do not overlap
 void launch_apply_full(const double *in, double *out, const void *links, const LatGeom &g, int nrhs, double kappa,
                        bool dag, hipStream_t s);
@@ -367,7 +366,6 @@ struct SolveBatch {
     const double2 *bh[FL_MAXLAT] = {nullptr, nullptr, nullptr, nullptr};
     double2 *xh[FL_MAXLAT] = {nullptr, nullptr, nullptr, nullptr};
     std::vector<double> bnorm;  // |b| of the full source, per system (host)
-    bool same_bits = false;     // a system's result may not depend on the rest of the batch in the last bit
 };
 
 struct SysResult {

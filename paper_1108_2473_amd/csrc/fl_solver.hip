@@ -70,7 +70,6 @@ struct Solver {
     int *active = nullptr, *mask = nullptr;
     SysState *st_alt = nullptr;  // the copy that the next folded beta step writes
     int *act_alt = nullptr;
-    bool split = false;     // small grids: hops of the iteration with a wave per direction
     bool fold = false;      // small grids: scalar steps inside the vector kernels
     bool fold_cgz = false;  // and CGNR's alpha inside the hop that updates z
     PinArr<SysState> hst;
@@ -106,7 +105,7 @@ struct Solver {
         }
         a.B.rev = flip;
         flip ^= 1;
-        dslash_config(c0, f, a, split && lo);
+        dslash_config(c0, f, a, lo);
         if (epi & EPI_CGZ) {
             a.fold = fold_cgz;
             a.active = active;
@@ -311,17 +310,14 @@ fl_status Solver::prepare()
     nsys = 0;
     for (int l = 0; l < sb.nlat; ++l) nsys += sb.nrhs[l];
     if (nsys == 0) return FL_OK;
-    // The 16-bit hop gives the same bits with a wave per direction, the folded
-    // steps do in every precision: results don't depend on the batch.  The FP64
-    // and FP32 hops round differently, so they run a wave per direction only
-    // for fewer than 4 right-hand sides (whose FP64 hops have always differed,
-    // by their LDS windows), and never where truncated solves are compared.
+    // Small grids: hops with a wave per direction and scalar steps inside the
+    // vector kernels.  Both give the bits of the other kernels in every
+    // precision: a system's result does not depend on its batch.
     {
-        split = fmt == LINK_Q16_R12 || (!sb.same_bits && !prm.truncated);
         DslashArgs a;
         std::memset(&a, 0, sizeof(a));
         a.B = B;
-        dslash_config(c0, fmt, a, split);
+        dslash_config(c0, fmt, a, true);
         // a folded step costs every wave a look at all the partial sums of its
         // system, a launch of its own about 5 us: folded up to 512 site blocks
         // (16^3x32 has 1024: 4.61 ms against 4.48 for one FP64 solve) and

@@ -95,7 +95,7 @@ __device__ __forceinline__ void link_mul(const cx<R> U[3][3], const cx<R> h[6], 
     for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            cx<R> acc = U[a][0] * h[3 * sp];
+            cx<R> acc = cmul(U[a][0], h[3 * sp]);
             acc = cmad(acc, U[a][1], h[3 * sp + 1]);
             acc = cmad(acc, U[a][2], h[3 * sp + 2]);
             w[3 * sp + a] = acc;
@@ -110,7 +110,7 @@ __device__ __forceinline__ void link_adj_mul(const cx<R> U[3][3], const cx<R> h[
     for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            cx<R> acc = cjmul(U[0][a], h[3 * sp]);
+            cx<R> acc = ccmul(U[0][a], h[3 * sp]);
             acc = cjmad(acc, U[1][a], h[3 * sp + 1]);
             acc = cjmad(acc, U[2][a], h[3 * sp + 2]);
             w[3 * sp + a] = acc;
