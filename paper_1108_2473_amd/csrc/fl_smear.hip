@@ -45,14 +45,16 @@ __device__ __forceinline__ void colour_hop(cx<double> acc[12], const cx<double> 
     for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            cx<double> v = ADJ ? cjmul(U[0][a], psi[3 * s]) : U[a][0] * psi[3 * s];
+            cx<double> v = ADJ ? ccmul(U[0][a], psi[3 * s]) : cmul(U[a][0], psi[3 * s]);
 #pragma unroll
             for (int b = 1; b < 3; ++b) v = ADJ ? cjmad(v, U[b][a], psi[3 * s + b]) : cmad(v, U[a][b], psi[3 * s + b]);
             acc[3 * s + a] = cx<double>{fma(alpha, v.re, acc[3 * s + a].re), fma(alpha, v.im, acc[3 * s + a].im)};
         }
 }
 
-// one step of (1 + alpha H) / norm for the sites of parity `par`.  A
+// one step of (1 + alpha H) / norm for the sites of parity `par`: alpha times each
+// of the six products added to psi, in the order z, x, y, forward before backward
+// (k_smear_plane has the same order, so the same bits).  A
 // workgroup is a tile of FL_WAVE sites x SM_RT right-hand sides (one wave
 // each), tiles in XCD-contiguous order with the right-hand-side groups of a
 // site block consecutive: the links of a site block are read by its waves
@@ -72,7 +74,8 @@ __global__ __launch_bounds__(BLK) void k_smear(SmearArgs a)
     cx<double> acc[12], psi[12], U[3][3];
     SpinorFmt<double>::load(a.same + rhs * fs, g.Vh, i, acc);
     const int Lh0 = g.Lh0, xh = c.x >> 1, Ly = g.L[1], Lz = g.L[2];
-    for (int mu = 0; mu < 3; ++mu) {
+    for (int d = 0; d < 3; ++d) {
+        const int mu = d == 0 ? 2 : d - 1;  // z, x, y: the order of k_smear_plane
         int nf, nb;
         if (mu == 0) {
             const int xf = (c.x + 1 == g.L[0]) ? 0 : c.x + 1, xb = (c.x == 0) ? g.L[0] - 1 : c.x - 1;
@@ -132,23 +135,20 @@ struct PlaneArgs {
     double alpha, inv_norm;
 };
 
-// acc += M v, M = U or U^+ (one colour vector)
-template <bool ADJ>
-__device__ __forceinline__ void colour_mad(cx<double> acc[3], const cx<double> U[9], const cx<double> v[3])
+// acc += alpha h (one colour vector)
+__device__ __forceinline__ void colour_add(cx<double> acc[3], double alpha, const cx<double> h[3])
 {
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) acc[a] = ADJ ? cjmad(acc[a], U[3 * b + a], v[b]) : cmad(acc[a], U[3 * a + b], v[b]);
+    for (int a = 0; a < 3; ++a) acc[a] = cx<double>{fma(alpha, h[a].re, acc[a].re), fma(alpha, h[a].im, acc[a].im)};
 }
 
-// h = M v
+// h = M v, M = U or U^+
 template <bool ADJ>
 __device__ __forceinline__ void colour_mul(cx<double> h[3], const cx<double> U[9], const cx<double> v[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        h[a] = ADJ ? cjmul(U[a], v[0]) : U[3 * a] * v[0];
+        h[a] = ADJ ? ccmul(U[a], v[0]) : cmul(U[3 * a], v[0]);
 #pragma unroll
         for (int b = 1; b < 3; ++b) h[a] = ADJ ? cjmad(h[a], U[3 * b + a], v[b]) : cmad(h[a], U[3 * a + b], v[b]);
     }
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(PL_T, 2) void k_smear_plane(PlaneArgs a)
     const double2 *wyf = lds + PL_SLOT * syf, *wyb = lds + PL_SLOT * syb + 6;
     const int hop = PL_SLOT * nslot;  // from one LDS buffer to the other
     const int c0 = part * a.cc, c1 = min(c0 + a.cc, a.ncomp);
-    cx<double> cur[3], acc[3], nc[3], nu[3], nd[3];
+    cx<double> acc[3], nc[3], nu[3], nd[3];
     v4f r[3] = {};
     auto fetch = [&](int c) {
         const Buf f = make_buf(a.in + (size_t)(c >> 2) * 24 * Vh, 2u * (unsigned)ps);
@@ -217,20 +217,22 @@ __global__ __launch_bounds__(PL_T, 2) void k_smear_plane(PlaneArgs a)
         plane_load<3>(f, up, so, cs, nu);
         plane_load<3>(f, dn, so, cs, nd);
     };
-    // the z terms of the fetched component, and its plane terms left in LDS
+    // psi of the fetched component with its z terms, and its plane terms left in LDS
     auto enter = [&](int b) {
         cx<double> h[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) cur[k] = nc[k];
-        colour_mul<false>(acc, Uz, nu);
-        colour_mad<true>(acc, Ud, nd);
+        for (int k = 0; k < 3; ++k) acc[k] = nc[k];
+        colour_mul<false>(h, Uz, nu);
+        colour_add(acc, a.alpha, h);
+        colour_mul<true>(h, Ud, nd);
+        colour_add(acc, a.alpha, h);
         double2 *q = w + b * hop;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) q[k] = make_double2(cur[k].re, cur[k].im);
-        colour_mul<true>(h, Ux, cur);
+        for (int k = 0; k < 3; ++k) q[k] = make_double2(nc[k].re, nc[k].im);
+        colour_mul<true>(h, Ux, nc);
 #pragma unroll
         for (int k = 0; k < 3; ++k) q[3 + k] = make_double2(h[k].re, h[k].im);
-        colour_mul<true>(h, Uy, cur);
+        colour_mul<true>(h, Uy, nc);
 #pragma unroll
         for (int k = 0; k < 3; ++k) q[6 + k] = make_double2(h[k].re, h[k].im);
     };
@@ -245,27 +247,23 @@ __global__ __launch_bounds__(PL_T, 2) void k_smear_plane(PlaneArgs a)
         if (more) fetch(c + 1);
         lds_barrier();
         const int b = (c & 1) * hop;
-        {
-            cx<double> q[3];
+        auto plane_terms = [&](const cx<double> U[9], const double2 *f, const double2 *bk) {
+            cx<double> q[3], h[3], e[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const double2 u = wxf[b + k], d = wxb[b + k], e = wyb[b + k];
+                const double2 u = f[b + k], d = bk[b + k];
                 q[k] = cx<double>{u.x, u.y};
-                acc[k].re += d.x + e.x;
-                acc[k].im += d.y + e.y;
+                e[k] = cx<double>{d.x, d.y};
             }
-            colour_mad<false>(acc, Ux, q);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double2 u = wyf[b + k];
-                q[k] = cx<double>{u.x, u.y};
-            }
-            colour_mad<false>(acc, Uy, q);
-        }
+            colour_mul<false>(h, U, q);
+            colour_add(acc, a.alpha, h);
+            colour_add(acc, a.alpha, e);
+        };
+        plane_terms(Ux, wxf, wxb);
+        plane_terms(Uy, wyf, wyb);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-            r[k] = d2_to_v4f(make_double2(fma(a.alpha, acc[k].re, cur[k].re) * a.inv_norm,
-                                          fma(a.alpha, acc[k].im, cur[k].im) * a.inv_norm));
+            r[k] = d2_to_v4f(make_double2(acc[k].re * a.inv_norm, acc[k].im * a.inv_norm));
         const Buf f = make_buf(a.out + (size_t)(c >> 2) * 24 * Vh, 2u * (unsigned)ps);
         store_fence_begin();
 #pragma unroll

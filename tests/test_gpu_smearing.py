@@ -142,3 +142,28 @@ def test_pion_correlator_with_ape_links(F):
     lat.set_gauge(U)
     assert np.abs(lat.smear(psi, 4.0, 3, 25.0) - O.smear(U, psi, dims, 4.0, 3, 25.0)).max() <= 1e-12
     lat.close()
+
+
+@pytest.mark.parametrize("dims,tile", [((8, 8, 4, 4), (4, 2)), ((6, 10, 6, 2), (3, 2)), ((16, 16, 2, 2), (2, 1)),
+                                       ((2, 2, 4, 2), (10, 14))])
+def test_smearing_same_sums_on_every_plane_size(F, dims, tile):
+    """A periodic field repeated in x and y until its planes exceed 256 sites:
+    the kernel for whole planes and the one for larger planes form the same
+    sums, bit for bit, so the accuracy does not depend on the lattice's shape."""
+    big = (dims[0] * tile[0], dims[1] * tile[1]) + dims[2:]
+    assert dims[0] * dims[1] <= 256 < big[0] * big[1]
+
+    def repeat(f):  # [n][V]... -> the repeated lattice
+        g = f.reshape((f.shape[0],) + dims[::-1] + f.shape[2:])
+        g = np.tile(g, (1, 1, 1, tile[1], tile[0]) + (1,) * (f.ndim - 2))
+        return np.ascontiguousarray(g.reshape((f.shape[0], -1) + f.shape[2:]))
+
+    U = S.random_links(dims, 0.5, 43)
+    psi = S.random_spinors(dims, 2, 44)
+    out = []
+    for d, links, field in ((dims, U, psi), (big, repeat(U), repeat(psi))):
+        lat = F.Lattice(d, -1)
+        lat.set_gauge(links)
+        out.append(lat.smear(field, 4.0, 7, 25.0))
+        lat.close()
+    assert np.array_equal(repeat(out[0]), out[1])
