@@ -847,7 +847,9 @@ struct LinkQ16R12 {
     // in words 2e, 2e + 1 of entry e = 3a + b of the matrix applied
     static constexpr float HALF_UNIT = 2.0f / 32767.0f;
     static constexpr int PK_SNC = 18;
-    // All in integers: rows 0 and 1 halved with rounding, row 2 (the conjugate
+    // All in integers: rows 0 and 1 halved, ties to even (half of all entries are
+    // ties: rounded up, they would shift every entry by 1/4 unit on average, the
+    // operator coherently), row 2 (the conjugate
     // cross product) from exact int16 products summed in int32 (below 2^30:
     // each entry of a unit matrix times 32767^2), rounded once to half scale;
     // about 75 vector instructions a link where the decode to FP32, the FP32
@@ -858,7 +860,10 @@ struct LinkQ16R12 {
         const s2 r[6] = {as_s2(v[0].x), as_s2(v[0].y), as_s2(v[1].x), as_s2(v[1].y), as_s2(v[2].x), as_s2(v[2].y)};
         s2 u[9];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) u[e] = __builtin_elementwise_add_sat(r[e], (s2){1, 1}) >> 1;
+        for (int e = 0; e < 6; ++e) {
+            const s2 h = r[e] >> 1;
+            u[e] = h + (r[e] & h & (s2){1, 1});
+        }
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             // conj(x y - z q), x, z of row 0 and y, q of row 1
