@@ -80,7 +80,7 @@ __device__ __forceinline__ void rows_put(v4f *sh, const Rows &r, const v4f v[12]
 {
 #pragma unroll
     for (int k = 0; k < 12; ++k) sh[(r.s[k % 3] + 16 * (k / 3)) * FA_ST + r.w[k % 3]] = v[k];
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 }
 
 // link of direction slot D
@@ -110,7 +110,7 @@ __device__ __forceinline__ void full_hop(const Buf &in, const Buf &gauge, const 
         const double2 d = v4f_to_d2(sh[r.lane * FA_ST + k]);
         psi[k] = cx<double>{d.x, d.y};
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     LinkF64R18::unpack(lv, U);
     project<MU, SGN>(psi, h);
     if constexpr (D & 1)
@@ -132,7 +132,7 @@ __device__ __forceinline__ void store_canon(const Buf &in, const Rows &r, double
     for (int k = 0; k < 12; ++k) v[k] = buf_ld16(in, i0 * 192 + (k * FL_WAVE + r.lane) * 16, 0);
 #pragma unroll
     for (int k = 0; k < 12; ++k) sh[r.lane * FA_ST + k] = d2_to_v4f(double2{acc[k].re, acc[k].im});
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
         const double2 d = v4f_to_d2(sh[(r.s[k % 3] + 16 * (k / 3)) * FA_ST + r.w[k % 3]]), p = v4f_to_d2(v[k]);
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(8 * FL_WAVE) void k_apply_split(const double *in, d
     add(std::integral_constant<int, 5>());
     add(std::integral_constant<int, 6>());
     add(std::integral_constant<int, 7>());
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     store_canon(b, make_rows(), out + (size_t)rhs * V * 24, i0, V, kappa, acc, shm);
 }
 

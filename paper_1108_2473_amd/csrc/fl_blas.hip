@@ -298,6 +298,7 @@ __device__ __forceinline__ void store_state(SysState *dst, const SysState &s, Sy
     constexpr int NW = (int)(sizeof(SysState) / 8);
     const int lane = threadIdx.x % FL_WAVE;
     if (lane == 0) *sh = s;
+    wave_sync();
     if (lane < NW) {
         unsigned long long w;
         __builtin_memcpy(&w, (const char *)sh + 8 * lane, 8);
@@ -689,6 +690,7 @@ __global__ __launch_bounds__(256) void k_scal(ScalArgs a)
     }
     // the flag store completes before the state is written as one store
     // instruction of 8-byte words, one per lane, which ends the kernel
+    wave_sync();
     store_drain();
     if ((int)threadIdx.x < NW)
         ((unsigned long long *)(a.st + sys))[threadIdx.x] = ((const unsigned long long *)&snew)[threadIdx.x];

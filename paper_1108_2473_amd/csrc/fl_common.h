@@ -181,6 +181,16 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// LDS handed from lane to lane within a wave: what was written before is read
+// after.  A lane that writes nothing itself gives the compiler no other reason
+// to keep its loads behind the writing lanes' stores
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // N 16-byte vectors of one lane at byte offsets voff + c * cstride (cstride
 // wave-uniform), as one store group
 template <int N, int CP = 0>
