@@ -329,10 +329,13 @@ fl_status fl_bench_dslash(fl_ctx *ctx, int prec, int gauge_reals, int nrhs, int 
  * FL_ERR_ARG for out-of-range values or lds 3 with another precision. */
 fl_status fl_set_tile(fl_ctx *ctx, int prec, int gauge_reals, int rt, int group, int lds);
 
-/* Autotuner: time the hopping kernel for nrhs right-hand sides over the
- * workgroup shapes and LDS modes above and keep the fastest for this
- * context (returned in rt, group, lds and its launch time in ms; any output
- * pointer may be NULL). */
+/* Autotuner: time the hopping kernel for nrhs right-hand sides in the built-in
+ * choice and over the workgroup shapes and LDS modes above and keep the fastest
+ * for this context (returned in rt, group, lds and its launch time in ms; any
+ * output pointer may be NULL).  The built-in choice stays unless another is
+ * faster by 3 %: rt and group are then 0 and lds tells how its workgroups of
+ * several right-hand sides stage their data; fl_set_tile(..., 0, 0, -1)
+ * restores it.  An error leaves the earlier choice. */
 fl_status fl_autotune(fl_ctx *ctx, int prec, int gauge_reals, int nrhs, int *rt, int *group,
                       int *lds, double *ms);
 

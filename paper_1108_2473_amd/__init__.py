@@ -485,8 +485,9 @@ class Lattice:
         self._check(lib().fl_set_tile(self._h, prec, gauge_reals, rt, group, lds))
 
     def autotune(self, prec=PREC_F32, gauge_reals=12, nrhs=1, cache=None):
-        """Time the hopping kernel over workgroup shapes and LDS modes and keep
-        the fastest for this lattice (fl_autotune).  cache: path of a JSON file
+        """Time the hopping kernel in the built-in choice and over workgroup shapes
+        and LDS modes and keep the fastest for this lattice (fl_autotune; rt 0: the
+        built-in choice).  cache: path of a JSON file
         of earlier results keyed by device name, lattice extents, precision,
         link reals and right-hand sides; a hit applies the stored shape
         (fl_set_tile) without timing, a miss times and adds its result."""
@@ -495,7 +496,7 @@ class Lattice:
             key = tune_key(_device_name(self.device), self.dims, prec, gauge_reals, nrhs, version())
             hit = tune_cache_load(cache).get(key)
             if hit is not None:
-                self.set_tile(prec, gauge_reals, hit["rt"], hit["group"], hit["lds"])
+                self.set_tile(prec, gauge_reals, hit["rt"], hit["group"], hit["lds"] if hit["rt"] else -1)
                 return dict(hit, cached=True)
         rt, g, ld, ms = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), ctypes.c_double()
         self._check(lib().fl_autotune(self._h, prec, gauge_reals, nrhs, ctypes.byref(rt), ctypes.byref(g),

@@ -1551,8 +1551,23 @@ fl_status fl_autotune(fl_ctx *c, int prec, int gauge_reals, int nrhs, int *rt_ou
     LinkFormat fmt;
     if ((e = fmt_of(c, prec, gauge_reals, &fmt))) return e;
     const int maxrt = fmt == LINK_F64_R18 ? 8 : 16;
-    double best = 1e300;
-    int brt = 0, bg = 0, bl = 0;
+    const int old[3] = {c->tune_rt[fmt], c->tune_g[fmt], c->tune_lds[fmt]};
+    auto keep = [&](int rt, int group, int lds) {
+        c->tune_rt[fmt] = rt;
+        c->tune_g[fmt] = group;
+        c->tune_lds[fmt] = lds;
+    };
+    auto fail = [&](fl_status err) {
+        keep(old[0], old[1], old[2]);
+        return err;
+    };
+    keep(0, 0, -1);
+    int brt = 0, bg = 0, bl = -1;
+    double best = 0, builtin = 0;
+    // the built-in choice may take shapes that can't be pinned (6 right-hand
+    // sides a workgroup, a wave per direction)
+    if ((e = bench_impl(c, fmt, nrhs, 6, 2, 0, 0, -1, &builtin, nullptr))) return fail(e);
+    best = builtin;
     for (int lds = 0; lds <= 4; ++lds)
         for (int rt = 1; rt <= maxrt; rt *= 2) {
             if (lds == 3 && fmt != LINK_Q16_R12) break;
@@ -1564,7 +1579,7 @@ fl_status fl_autotune(fl_ctx *c, int prec, int gauge_reals, int nrhs, int *rt_ou
                 // two buffer sets larger than the on-chip caches, a few repetitions
                 e = bench_impl(c, fmt, nrhs, 6, 2, rt, gg, lds, &ms, nullptr);
                 if (e == FL_ERR_ARG) break;  // staging does not fit this shape
-                if (e) return e;
+                if (e) return fail(e);
                 if (ms < best) {
                     best = ms;
                     brt = rt;
@@ -1575,13 +1590,34 @@ fl_status fl_autotune(fl_ctx *c, int prec, int gauge_reals, int nrhs, int *rt_ou
             }
         }
     c->err.clear();
-    c->tune_rt[fmt] = brt;
-    c->tune_g[fmt] = bg;
-    c->tune_lds[fmt] = bl;
+    // a shape is pinned if it stays faster over more launches, by more than
+    // repeated timings differ (the sweep's few launches of a small grid scatter)
+    for (int k = 0; brt && k < 3; ++k) {
+        double b = 0, m = 0;
+        if ((e = bench_impl(c, fmt, nrhs, 30, 2, 0, 0, -1, &b, nullptr)) ||
+            (e = bench_impl(c, fmt, nrhs, 30, 2, brt, bg, bl, &m, nullptr)))
+            return fail(e);
+        builtin = k ? std::min(builtin, b) : b;
+        best = k ? std::min(best, m) : m;
+    }
+    if (brt && !(best < 0.97 * builtin)) {
+        brt = bg = 0;
+        bl = -1;
+    }
+    keep(brt, bg, bl);
+    if (!brt) {  // reported: the staging of its workgroups that share links
+        int RT, G;
+        tile_shape(c, fmt, nrhs, &RT, &G);
+        DslashArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.B = batch_geom(&c, &nrhs, 1, RT, G);
+        dslash_config(c, fmt, a, false);
+        bl = a.lds;
+    }
     if (rt_out) *rt_out = brt;
     if (group_out) *group_out = bg;
     if (lds_out) *lds_out = bl;
-    if (ms_out) *ms_out = best;
+    if (ms_out) *ms_out = brt ? best : builtin;
     return FL_OK;
 }
 
