@@ -109,3 +109,38 @@ def test_staged_16bit_links_are_unbiased(F):
     shift = (schur(up) - schur(U))[even].mean(axis=0)
     got = (out[4] - out[0])[even].mean(axis=0)
     assert abs(np.vdot(shift, got)) <= 0.1 * np.vdot(shift, shift).real
+
+
+@pytest.mark.parametrize("nrhs", [9, 12, 17, 20])
+def test_16bit_workgroups_of_four(F, nrhs):
+    """The workgroups of 4 right-hand sides that the 16-bit hop takes for these
+    counts, the last one partly filled (lds=4 keeps the built-in workgroup and
+    turns the wave per direction off), against workgroups of 8 and a wave per
+    direction."""
+    dims = (6, 4, 4, 6)
+    lat = make(F, dims)
+    psi = S.random_spinors(dims, nrhs, 75)
+    prm = F.SolverParams(inner_prec=3, gauge_reals=12)
+    split = lat.apply_schur(psi, prm)
+    lat.set_tile(prec=3, gauge_reals=12, lds=4)
+    four = lat.apply_schur(psi, prm)
+    lat.set_tile(prec=3, gauge_reals=12, rt=8)
+    eight = lat.apply_schur(psi, prm)
+    lat.close()
+    assert np.array_equal(four, split)
+    assert np.array_equal(four, eight)
+
+
+def test_noalloc_scratch_is_reused(F):
+    """Result over the input: the work fields in the fixed scratch array, which
+    the second, smaller call finds as the first left them."""
+    import torch
+    dims = (8, 8, 8, 16)
+    lat = make(F, dims)
+    for nrhs, seed in ((16, 76), (3, 77)):
+        psi = torch.from_numpy(S.random_spinors(dims, nrhs, seed)).cuda()
+        want = lat.apply_D(psi)
+        lat.apply_D_noalloc(psi, psi)
+        torch.cuda.synchronize()
+        assert torch.equal(psi, want)
+    lat.close()
