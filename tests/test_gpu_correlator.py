@@ -117,3 +117,16 @@ def test_exact_loop_correlator_4x4x4x8(F):
     # gamma_5 loops are real for exact loops, so the g5-g5 zero-momentum correlator is real
     assert np.abs(D[0, 0].imag).max() <= 1e-9 * np.abs(D[0, 0]).max()
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(1020, 2, 2, 2), (2, 1020, 2, 2), (2, 2, 1020, 2), (512, 510, 2, 2)])
+def test_projection_largest_extents(F, dims):
+    """Lx + Ly + Lz = 1024: phase tables of 64 KB for the four momenta of a workgroup."""
+    Vs, T = dims[0] * dims[1] * dims[2], dims[3]
+    mom = [(0, 0, 0), (1, -1, 1), (511, 3, -2), (-509, 1, 0), (7, 513, 1)]
+    lat = F.Lattice(dims, -1)
+    L = _rand((2, T, Vs), 16)
+    P = lat.momentum_project(L, mom)
+    W = O.momentum_project(L, dims, mom)
+    lat.close()
+    assert np.abs(P - W).max() <= 1e-12 * np.sqrt(Vs)
