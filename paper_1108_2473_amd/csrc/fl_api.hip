@@ -388,11 +388,13 @@ BatchGeom batch_geom(fl_ctx *const *ctx, const int *nrhs, int nlat, int RT, int 
     return B;
 }
 
-// Largest number of 64-site tiles for which the hop runs a wave per direction.
-// Whole solves, before -> after: FP64 8^3x16, 64 tiles, 1.84 -> 1.72 ms, 324
-// tiles 3.06 -> 2.78, 768 tiles 3.03 -> 3.60 (links read once per right-hand
-// side, and waves enough without it); 16-bit 64 tiles 4.69 -> 3.51, 1024 tiles
-// 6.23 -> 5.46; FP32 64 tiles 1.96 -> 1.63, 1024 tiles 3.88 -> 2.78
+// Largest number of 64-site tiles for which the hop runs a wave per direction;
+// beyond it there are waves enough without, and links are read once per
+// right-hand side.  Iterations without : with it on nine lattices (CGNR; FP64 and
+// FP32 up to 3 right-hand sides, 16-bit up to 16): FP64 256 tiles 1.16, 324 and
+// 343 1.11, 357 0.98, 512 1.00-1.04, 648 0.83-0.96; FP32 512 tiles 1.16-1.28, 768
+// 1.06, 1024 1.00-1.42, 1029 0.97; 16-bit 512 tiles 1.13-1.21, 768 1.01, 952 1.05,
+// 1024 1.01-1.15, 1029 0.96
 static int split_tiles(LinkFormat fmt) { return fmt == LINK_F64_R18 ? 330 : 1024; }
 
 void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G)
@@ -415,7 +417,10 @@ void tile_shape(const fl_ctx *c, int fmt, int nrhs, int *RT, int *G)
         // 8-wave workgroup's, measured on the hop at 16^3x32: 4 waves 57
         // (16-bit), 60 (FP32), 50 (FP64), 6 waves 80 (FP32) and 77 (FP64; 97
         // for 16-bit).  12 right-hand sides: 16-bit 35.0 us in blocks of 8,
-        // 30.4 of 4; FP32 59.3, 49.4 of 6; FP64 148, 124 of 4
+        // 30.4 of 4; FP32 58.0, 47.9 of 6; FP64 148, 124 of 4.  On five smaller
+        // lattices, 9 to 41 right-hand sides, iterations take 0.76 to 1.01 of
+        // the time in blocks of 8, but for FP64 on 8^4 (33, 36) and 8^3x16 (20):
+        // 1.04-1.05
         const int six = fmt == LINK_Q16_R12 ? 97 : (fmt == LINK_F64_R18 ? 77 : 80);
         const int four = fmt == LINK_Q16_R12 ? 57 : (fmt == LINK_F64_R18 ? 50 : 60);
         int best = 100 * ((nrhs + 7) / 8);

@@ -12,8 +12,9 @@
 //   p = r + beta (p - omega v)
 // with the operator launches in fl_dslash.hip carrying the reductions in
 // their epilogue.  Reductions are two-stage and deterministic: each
-// wavefront writes one partial per 64-site block, and one workgroup per
-// system sums the partials in a fixed order.
+// wavefront writes one partial per 64-site block, and the partials of a system
+// are summed in a fixed order by one workgroup (k_scal) or, on small grids, by
+// every wave that needs the sum (FoldedStep), with the same bits.
 #include "fl_host.h"
 
 namespace {

@@ -653,8 +653,7 @@ __host__ __device__ __forceinline__ float bf16_to_f32(uint32_t h)
 template <typename R>
 __device__ __forceinline__ void rebuild_row2(cx<R> U[3][3])
 {
-    // row2 = conj(row0 x row1), the same roundings in every kernel; the
-    // imaginary part a.im b.re + a.re b.im (the order of the factors of cmul)
+    // row2 = conj(row0 x row1), with the same roundings in every kernel
     U[2][0] = cj(cmsub(cmul(U[1][2], U[0][1]), U[0][2], U[1][1]));
     U[2][1] = cj(cmsub(cmul(U[1][0], U[0][2]), U[0][0], U[1][2]));
     U[2][2] = cj(cmsub(cmul(U[1][1], U[0][0]), U[0][1], U[1][0]));
@@ -847,7 +846,7 @@ struct LinkQ16R12 {
 #pragma unroll
         for (int e = 0; e < 9; ++e) U[e / 3][e % 3] = h16_pair(w[e]);
     }
-    // staged form of the packed integer hop: at half scale, round(16383.5 u)
+    // staged form of the packed integer hop: half the stored integers
     // (|entry| <= 16384), each entry as the two int16 pairs whose dot
     // products with a colour component h = (hr, hi) give the real and the
     // imaginary part of the product: for the link itself (forward hop)

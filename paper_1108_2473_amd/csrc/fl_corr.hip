@@ -8,11 +8,12 @@
 // per-axis factors exp(2 pi i r_mu / L_mu), r_mu = (n_mu x_mu) mod L_mu,
 // each evaluated once per workgroup by sincospi on the exactly reduced
 // argument 2 r_mu / L_mu and kept in LDS (two complex products per site
-// instead of a sine and cosine).  Sums run in FP64 in a fixed order
-// (per-thread partial sums over a strided site range, then a fixed tree in
-// LDS), so results do not depend on the launch.
+// instead of a sine and cosine).  Sums run in FP64 in a fixed order (a
+// thread's columns along z, then a wave's lanes by pairwise exchanges, then the
+// four waves), so results do not depend on the launch.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "fl_host.h"
 
@@ -21,7 +22,7 @@ namespace {
 constexpr int MAXG = 16;    // Gamma matrices per call
 constexpr int BLK = 256;
 constexpr int MAXAX = 1024;  // Lx + Ly + Lz: the per-axis phase tables in LDS (16 KB a momentum)
-constexpr int MB = 4;        // momenta per workgroup of the projection
+constexpr int MOMS = 4;      // momenta per workgroup of the projection (of more than one)
 constexpr int MCH = 64;      // momenta, or Gamma pairs, per launch: they travel as kernel arguments
 
 struct MomArgs {
@@ -32,18 +33,24 @@ struct MomArgs {
     unsigned short mom[MCH][4];  // reduced to 0 .. L_mu - 1
 };
 
+// real and imaginary part of the product of a phase and a value
+__device__ __forceinline__ double phase_re(double2 p, double2 l) { return fma(p.x, l.x, -(p.y * l.y)); }
+__device__ __forceinline__ double phase_im(double2 p, double2 l) { return fma(p.x, l.y, p.y * l.x); }
+
 // one workgroup per (timeslice, MB momenta, group of GB Gammas), in
 // XCD-contiguous order with the Gamma group innermost, then the momenta: each
 // XCD takes a run of timeslices, so a timeslice's loops (ngamma x V_s values)
 // come from HBM once and then from that XCD's L2, once for every MB momenta.
-// A thread keeps one (x, y) and its phase and walks along z.  Loads past the
-// last Gamma or momentum repeat it; its sum is not stored.  The sums of a
+// A thread walks along z with the phases of z and applies the phase of (x, y)
+// to the column's sum.  Loads past the last Gamma or momentum repeat it; its
+// sum is not stored.  The sums of a
 // thread's GB x MB values over the wave halve the number of values per lane at
 // every exchange: 32 doubles take 32 exchanges instead of 192.  Bound by
 // instruction issue and the start of its short workgroups: 16^3x32 with 6
-// Gammas and 33 momenta 15.7 us (31.5 us with one momentum a workgroup, which
-// drew 13 TB/s from L2; 21.7 us with three table reads a site).
-template <int GB>
+// Gammas and 33 momenta 39 us a call with its wait (59 with one momentum a
+// workgroup, which drew 13 TB/s from L2).
+// ONE: planes of up to BLK sites, one column a thread.
+template <int GB, int MB, bool ONE>
 __global__ __launch_bounds__(BLK) void k_momproj(MomArgs a)
 {
     constexpr int NV = 2 * MB * 4;   // values of a lane, Gammas padded to 4 for the exchanges
@@ -72,35 +79,61 @@ __global__ __launch_bounds__(BLK) void k_momproj(MomArgs a)
     // planes of up to BLK sites: BLK / P threads share a column
     const int nz = a.P >= BLK ? 1 : BLK / a.P;
     const int z0 = a.P >= BLK ? 0 : (int)threadIdx.x / a.P;
+    const double2 *pz = ph + a.Lx + a.Ly;
     if (z0 < nz)
         for (int xy = (int)threadIdx.x - z0 * a.P; xy < a.P; xy += BLK) {
-            const int y = xy / a.Lx, x = xy - y * a.Lx;
-            double2 pxy[MB];
+            double own[ONE ? 1 : NV];
+            double *u = ONE ? v : own;  // the column's sums with the phases of z
 #pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const double2 px = ph[m * nL + x], py = ph[m * nL + a.Lx + y];
-                pxy[m] = make_double2(px.x * py.x - px.y * py.y, px.x * py.y + px.y * py.x);
-            }
-            const double2 *pz = ph + a.Lx + a.Ly;
-#pragma unroll 4
-            for (int z = z0; z < a.Lz; z += nz) {
-                double2 l[GB];
+            for (int k = 0; k < (ONE ? 0 : NV); ++k) u[k] = 0.0;
+            // two sites at a time; each term is rounded before it is added, so
+            // that one rounding in two sites has the size of the sum
+            int z = z0;
+#pragma unroll 1
+            for (; z + nz < a.Lz; z += 2 * nz) {
+                double2 l[2][GB];
 #pragma unroll
-                for (int j = 0; j < GB; ++j) l[j] = src[j][z * a.P + xy];
+                for (int j = 0; j < GB; ++j) {
+                    l[0][j] = src[j][z * a.P + xy];
+                    l[1][j] = src[j][(z + nz) * a.P + xy];
+                }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    const double2 q = pz[m * nL + z];
-                    const double cs = pxy[m].x * q.x - pxy[m].y * q.y, sn = pxy[m].x * q.y + pxy[m].y * q.x;
+                    const double2 p = pz[m * nL + z], q = pz[m * nL + z + nz];
 #pragma unroll
                     for (int j = 0; j < GB; ++j) {
-                        double *w = v + 2 * (m * 4 + j);
-                        w[0] = fma(cs, l[j].x, fma(-sn, l[j].y, w[0]));
-                        w[1] = fma(cs, l[j].y, fma(sn, l[j].x, w[1]));
+                        double *w = u + 2 * (m * 4 + j);
+                        w[0] += phase_re(p, l[0][j]) + phase_re(q, l[1][j]);
+                        w[1] += phase_im(p, l[0][j]) + phase_im(q, l[1][j]);
                     }
                 }
             }
+            if (z < a.Lz)
+#pragma unroll
+                for (int j = 0; j < GB; ++j) {
+                    const double2 l = src[j][z * a.P + xy];
+#pragma unroll
+                    for (int m = 0; m < MB; ++m) {
+                        const double2 p = pz[m * nL + z];
+                        u[2 * (m * 4 + j)] += phase_re(p, l);
+                        u[2 * (m * 4 + j) + 1] += phase_im(p, l);
+                    }
+                }
+            const int y = xy / a.Lx, x = xy - y * a.Lx;
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const double2 px = ph[m * nL + x], py = ph[m * nL + a.Lx + y];
+                const double2 p = make_double2(phase_re(px, py), phase_im(px, py));
+#pragma unroll
+                for (int j = 0; j < GB; ++j) {
+                    double *w = v + 2 * (m * 4 + j);
+                    const double2 c = make_double2(u[2 * (m * 4 + j)], u[2 * (m * 4 + j) + 1]);
+                    w[0] = (ONE ? 0.0 : w[0]) + phase_re(p, c);
+                    w[1] = (ONE ? 0.0 : w[1]) + phase_im(p, c);
+                }
+            }
         }
-    // lane l ends with the wave's sum of value l >> 1
+    // lane l ends with the wave's sum of value (l >> 1) % NV
     const int lane = threadIdx.x % FL_WAVE, wave = threadIdx.x / FL_WAVE;
 #pragma unroll
     for (int n = NV / 2; n >= 1; n /= 2) {
@@ -111,19 +144,19 @@ __global__ __launch_bounds__(BLK) void k_momproj(MomArgs a)
             v[k] = mine + __shfl_xor(other, 2 * n, FL_WAVE);
         }
     }
+#pragma unroll
+    for (int n = FL_WAVE / 2; n > NV; n /= 2) v[0] += __shfl_xor(v[0], n, FL_WAVE);
     v[0] += __shfl_xor(v[0], 1, FL_WAVE);
     __shared__ double red[BLK / FL_WAVE][NV];
-    if ((lane & 1) == 0) red[wave][lane >> 1] = v[0];
+    if ((lane & 1) == 0 && (lane >> 1) < NV) red[wave][lane >> 1] = v[0];
     __syncthreads();
     // one store instruction, one value a lane, which ends the kernel
     if ((int)threadIdx.x >= NV / 2) return;
     const int m = threadIdx.x / 4, j = threadIdx.x % 4;
-    double2 o = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int w = 0; w < BLK / FL_WAVE; ++w) {
-        o.x += red[w][2 * threadIdx.x];
-        o.y += red[w][2 * threadIdx.x + 1];
-    }
+    static_assert(BLK == 4 * FL_WAVE, "four waves");
+    const int n = 2 * threadIdx.x;
+    const double2 o = make_double2((red[0][n] + red[1][n]) + (red[2][n] + red[3][n]),
+                                   (red[0][n + 1] + red[1][n + 1]) + (red[2][n + 1] + red[3][n + 1]));
     if (k0 + m < a.nk && j < GB && g0 + j < a.ngamma)
         a.Lp[((size_t)(g0 + j) * a.nmom + a.k0 + k0 + m) * a.nt + t] = o;
 }
@@ -176,9 +209,10 @@ void launch_momproj(const double2 *L, double2 *Lp, const int *mom, int ngamma, i
     a.Lz = L4[2];
     a.P = L4[0] * L4[1];
     a.Vs = a.P * L4[2];
-    const size_t shm = (size_t)MB * (L4[0] + L4[1] + L4[2]) * sizeof(double2);
     // Gammas per workgroup: as few groups of at most 4 as cover them, evenly
     const int ngr = (ngamma + 3) / 4, gb = (ngamma + ngr - 1) / ngr;
+    const int mb = MOMS;
+    const size_t shm = (size_t)mb * (L4[0] + L4[1] + L4[2]) * sizeof(double2);
     for (a.k0 = 0; a.k0 < nmom; a.k0 += MCH) {
         a.nk = std::min(MCH, nmom - a.k0);
         for (int k = 0; k < a.nk; ++k)
@@ -186,12 +220,25 @@ void launch_momproj(const double2 *L, double2 *Lp, const int *mom, int ngamma, i
                 const int r = mom[3 * (size_t)(a.k0 + k) + mu] % L4[mu];
                 a.mom[k][mu] = (unsigned short)(r < 0 ? r + L4[mu] : r);
             }
-        const dim3 grid((unsigned)(nt * ((a.nk + MB - 1) / MB) * ngr)), block(BLK);
+        const dim3 grid((unsigned)(nt * ((a.nk + mb - 1) / mb) * ngr)), block(BLK);
+        auto momenta = [&](auto n, auto m) {
+            constexpr int GB = decltype(n)::value, MB = decltype(m)::value;
+            if (a.P <= BLK)
+                hipLaunchKernelGGL((k_momproj<GB, MB, true>), grid, block, shm, s, a);
+            else
+                hipLaunchKernelGGL((k_momproj<GB, MB, false>), grid, block, shm, s, a);
+        };
+        auto launch = [&](auto n) {
+            if (mb == 1)
+                momenta(n, std::integral_constant<int, 1>());
+            else
+                momenta(n, std::integral_constant<int, MOMS>());
+        };
         switch (gb) {
-        case 1: hipLaunchKernelGGL(k_momproj<1>, grid, block, shm, s, a); break;
-        case 2: hipLaunchKernelGGL(k_momproj<2>, grid, block, shm, s, a); break;
-        case 3: hipLaunchKernelGGL(k_momproj<3>, grid, block, shm, s, a); break;
-        default: hipLaunchKernelGGL(k_momproj<4>, grid, block, shm, s, a); break;
+        case 1: launch(std::integral_constant<int, 1>()); break;
+        case 2: launch(std::integral_constant<int, 2>()); break;
+        case 3: launch(std::integral_constant<int, 3>()); break;
+        default: launch(std::integral_constant<int, 4>()); break;
         }
     }
 }

@@ -312,8 +312,8 @@ struct MemSrcQ16 {
 // The packed integer hop of 16-bit fields without windows (lds mode 4, the
 // built-in choice).  With a full chip it is held between vector issue (55-70 %
 // of the cycles) and the traffic behind L2, neither alone: at 16^3x32 with 384
-// right-hand sides 831 us a launch, with the link staging decoded to FP32
-// instead of done in integers 837; with few right-hand sides the staging is
+// right-hand sides 820-830 us a launch, the same with the link staging decoded
+// to FP32 instead of done in integers; with few right-hand sides the staging is
 // on the critical path (one: 8.0 against 10.7 us; 7 of 10x6x14x18: 6.9
 // against 7.4).  Issuing the first neighbour loads before the barrier: 3-8 %
 // faster below 100 MB of input, 5-7 % slower above (L2 holds less of what

@@ -36,8 +36,8 @@ __device__ __forceinline__ long long lex_of(const LatGeom &g, int x, int y, int 
 // site, both of checkerboard index m: the pairs are CV_P consecutive sites of
 // both parities on one side and 384 CV_P consecutive bytes on the other, and
 // LDS turns one order into the other.  Both sides move whole lines; bound by
-// memory (16^3x32, 12 right-hand sides, 604 MB: 105 us each way; writing the
-// canonical array site by site took 225 us).
+// memory (16^3x32, 12 right-hand sides, 604 MB: 98 to 110 us each way; writing
+// the canonical array site by site took 225 us).
 constexpr int CV_P = 128;
 constexpr int CV_ST = 13;  // 16-byte units from site to site in LDS (odd: no bank conflicts)
 

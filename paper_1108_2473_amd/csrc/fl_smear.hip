@@ -485,8 +485,8 @@ fl_status smear_canon(fl_ctx *c, double *canon, int nrhs, double alpha, int n, d
     const int P = c->L[0] * c->L[1];
     // planes of up to PL_T sites (16 x 16): the plane kernel, 138 us per step of
     // 12 fields at 16^3x32 against 296 us of the gather kernel's two launches;
-    // 4^3x8, one field: 4 against 9 us.  Larger planes have no workgroup that
-    // holds them
+    // 4^3x8, one field: 4 against 9 us.  Larger planes would take a workgroup of
+    // 512 threads and 147 KB of LDS, one per CU; that was not tried
     const size_t shm = (size_t)2 * PL_SLOT * PL_T * sizeof(double2);
     if (P <= PL_T && shm <= c->max_lds) {
         PlaneArgs a;

@@ -124,7 +124,7 @@ __device__ __forceinline__ void link_adj_mul(const cx<R> U[3][3], const cx<R> h[
 // int32 (v_dot2_i32_i16), converted to FP32 once per product component.
 // The fields store at most 16383 in magnitude, so no projected component
 // leaves the int16 range (|u| + |l| <= 32766), and the links are staged at
-// half scale, round(16383.5 u), which keeps every three-term sum of a
+// half scale (16383.5 u, rounded), which keeps every three-term sum of a
 // product row below sqrt(6) * 32766 * 16384 < 2^31
 // (Cauchy-Schwarz over the 6 reals of a unit row of U or U^+ and the 6
 // reals of a projected colour vector).  Each staged entry carries the two

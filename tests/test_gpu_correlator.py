@@ -124,9 +124,44 @@ def test_projection_largest_extents(F, dims):
     """Lx + Ly + Lz = 1024: phase tables of 64 KB for the four momenta of a workgroup."""
     Vs, T = dims[0] * dims[1] * dims[2], dims[3]
     mom = [(0, 0, 0), (1, -1, 1), (511, 3, -2), (-509, 1, 0), (7, 513, 1)]
+    mom += [(3 * k, k, 5 * k) for k in range(255)]  # enough for workgroups of four momenta
     lat = F.Lattice(dims, -1)
     L = _rand((2, T, Vs), 16)
     P = lat.momentum_project(L, mom)
     W = O.momentum_project(L, dims, mom)
     lat.close()
     assert np.abs(P - W).max() <= 1e-12 * np.sqrt(Vs)
+
+
+@pytest.mark.parametrize("nmom", [5, 300])
+def test_projection_rounds_once_per_site(F, nmom):
+    """Accuracy of a thread's sum over 480 sites along z: no worse than a plain FP64
+    evaluation in the same order, which rounds each site's term once into the
+    sum.  Two roundings per site would be 2 ** 0.5 = 1.41 times as far off; 1.2
+    separates them."""
+    dims, mom = (16, 16, 480, 2), [(0, 0, 1), (1, 0, 3), (-3, 5, 7), (2, 7, -100), (1, -1, 1)]
+    Vs, T = dims[0] * dims[1] * dims[2], dims[3]
+    L = _rand((3, T, Vs), 17)
+    lat = F.Lattice(dims, -1)
+    P = lat.momentum_project(L, mom + [(0, 0, k) for k in range(nmom - len(mom))])
+    lat.close()
+    ld = np.longdouble
+    two_pi = 2 * ld("3.14159265358979323846264338327950288")
+    f = L.reshape(3, T, dims[2], dims[1], dims[0])
+    err = np.zeros(2)
+    for k, n in enumerate(mom):
+        ph = []
+        for mu in range(3):
+            a = two_pi * ((n[mu] * np.arange(dims[mu])) % dims[mu]).astype(ld) / dims[mu]
+            ph.append(np.cos(a) + 1j * np.sin(a))
+        exact = f.astype(np.clongdouble)
+        for p in ph:
+            exact = (exact * p).sum(-1)
+        x, y, z = (p.astype(np.complex128) for p in ph)
+        xy = x[None, :] * y[:, None]
+        acc = np.zeros(f.shape[:2] + xy.shape, complex)
+        for i in range(dims[2]):
+            acc += f[:, :, i] * (xy * z[i])
+        err += [(np.abs(v.astype(np.clongdouble) - exact) ** 2).sum().astype(float)
+                for v in (P[:, k], acc.reshape(acc.shape[:2] + (-1,)).sum(-1))]
+    assert err[0] <= 1.2 ** 2 * err[1]
