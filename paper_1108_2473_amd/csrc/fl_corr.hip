@@ -211,7 +211,11 @@ void launch_momproj(const double2 *L, double2 *Lp, const int *mom, int ngamma, i
     a.Vs = a.P * L4[2];
     // Gammas per workgroup: as few groups of at most 4 as cover them, evenly
     const int ngr = (ngamma + 3) / 4, gb = (ngamma + ngr - 1) / ngr;
-    const int mb = MOMS;
+    // up to 512 workgroups (two per CU) a momentum has one to itself: four in one
+    // would leave CUs idle and, below four, compute repeats.  Calls with four and
+    // with one: 24^3x16, 16 Gammas, 2 momenta 52.7 and 39.3 us, 16^3x32, 6 Gammas,
+    // 5 momenta 29.0 and 27.0; above, 16^3x32, 6 Gammas, 33 momenta 39 and 59
+    const int mb = (long long)nt * ngr * nmom <= 512 ? 1 : MOMS;
     const size_t shm = (size_t)mb * (L4[0] + L4[1] + L4[2]) * sizeof(double2);
     for (a.k0 = 0; a.k0 < nmom; a.k0 += MCH) {
         a.nk = std::min(MCH, nmom - a.k0);

@@ -165,3 +165,20 @@ def test_projection_rounds_once_per_site(F, nmom):
         err += [(np.abs(v.astype(np.clongdouble) - exact) ** 2).sum().astype(float)
                 for v in (P[:, k], acc.reshape(acc.shape[:2] + (-1,)).sum(-1))]
     assert err[0] <= 1.2 ** 2 * err[1]
+
+
+@pytest.mark.parametrize("dims", [(18, 16, 4, 40), (2, 2, 4, 40), (6, 10, 2, 40), (16, 16, 2, 40), (4, 4, 6, 40)])
+@pytest.mark.parametrize("ng,nmom", [(1, 1), (1, 12), (1, 13), (3, 66), (5, 6), (5, 7), (16, 14)])
+def test_projection_momenta_per_workgroup(F, dims, ng, nmom):
+    """Both sides of the 512 workgroups up to which each momentum has its own,
+    and remainders of the groups of four momenta and of up to four Gammas, on
+    planes of one and of several columns a thread; odd and even numbers of
+    sites a thread."""
+    Vs, T = dims[0] * dims[1] * dims[2], dims[3]
+    mom = [((7 * k) % 41 - 20, (5 * k) % 37 - 18, (3 * k) % 31 - 15) for k in range(nmom)]
+    lat = F.Lattice(dims, -1)
+    L = _rand((ng, T, Vs), 18)
+    P = lat.momentum_project(L, mom)
+    W = O.momentum_project(L, dims, mom)
+    lat.close()
+    assert np.abs(P - W).max() <= 1e-12 * np.sqrt(Vs)
