@@ -128,8 +128,11 @@ def test_projection_largest_extents(F, dims):
     lat = F.Lattice(dims, -1)
     L = _rand((2, T, Vs), 16)
     P = lat.momentum_project(L, mom)
-    W = O.momentum_project(L, dims, mom)
     lat.close()
+    # the oracle takes the phases' arguments as they are, with an error that grows
+    # with n x: the same momenta within half the extents
+    red = [tuple((n + e // 2) % e - e // 2 for n, e in zip(k, dims)) for k in mom]
+    W = O.momentum_project(L, dims, red)
     assert np.abs(P - W).max() <= 1e-12 * np.sqrt(Vs)
 
 
