@@ -394,10 +394,14 @@ __global__ __launch_bounds__(128) void k_stoch_contract(StochContractArgs a)
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
-                for (int be = 0; be < 4; ++be)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        t[4 * al + be] = cjmad(t[4 * al + be], eta[3 * al + c], phi[3 * be + c]);
+                for (int be = 0; be < 4; ++be) {
+                    // the colour sum by itself: one rounding a right-hand side
+                    // has the size of the whole sum
+                    cx<double> v = ccmul(eta[3 * al], phi[3 * be]);
+                    v = cjmad(v, eta[3 * al + 1], phi[3 * be + 1]);
+                    v = cjmad(v, eta[3 * al + 2], phi[3 * be + 2]);
+                    t[4 * al + be] = t[4 * al + be] + v;
+                }
         };
         if (job[JOB_TARGET])
             add(acc[1]);
@@ -475,16 +479,22 @@ __device__ __forceinline__ void force_link(const ForceArgs &a, int par, int i, i
     cx<double> acc[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) acc[k] = cx<double>{0, 0};
-    auto outer = [&](const cx<double> u[6], const cx<double> v[6]) {  // acc_ij += u_i conj(v_j)
+    // acc_ij += sum of u_i conj(v_j) and p_i conj(q_j), the sum by itself: one
+    // rounding a right-hand side has the size of acc
+    auto outer = [&](const cx<double> u[6], const cx<double> v[6], const cx<double> p[6], const cx<double> q[6]) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) acc[3 * k + j] = cjmad(acc[3 * k + j], v[3 * s + j], u[3 * s + k]);
+            for (int j = 0; j < 3; ++j) {
+                cx<double> d = ccmul(v[j], u[k]);
+                d = cjmad(d, v[3 + j], u[3 + k]);
+                d = cjmad(d, q[j], p[k]);
+                d = cjmad(d, q[3 + j], p[3 + k]);
+                acc[3 * k + j] = acc[3 * k + j] + d;
+            }
     };
     for (int r = 0; r < a.nrhs; ++r) {
-        cx<double> p[12], q[12], u[6], v[6], w[12], z[12];
+        cx<double> p[12], q[12], u[6], v[6], w[12], z[12], hu[6], hv[6];
         SpinorFmt<double>::load(spinor_buf<double>(par ? a.co : a.ce, Vh, r), Vh, i, p);   // chi(x)
         SpinorFmt<double>::load(spinor_buf<double>(par ? a.pe : a.po, Vh, r), Vh, nf, q);  // psi(x + mu)
         SpinorFmt<double>::load(spinor_buf<double>(par ? a.po : a.pe, Vh, r), Vh, i, w);   // psi(x)
@@ -492,10 +502,9 @@ __device__ __forceinline__ void force_link(const ForceArgs &a, int par, int i, i
         __builtin_amdgcn_sched_barrier(0);
         project<MU, -1>(p, u);
         project<MU, -1>(q, v);
-        outer(u, v);
-        project<MU, 1>(w, u);
-        project<MU, 1>(z, v);
-        outer(u, v);
+        project<MU, 1>(w, hu);
+        project<MU, 1>(z, hv);
+        outer(u, v, hu, hv);
     }
     double2 *o = a.dU + ((size_t)MU * 2 * Vh + lex) * 9;
     double2 *ptr[9];
