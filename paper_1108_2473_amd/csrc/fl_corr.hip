@@ -47,7 +47,7 @@ __device__ __forceinline__ double phase_im(double2 p, double2 l) { return fma(p.
 // thread's GB x MB values over the wave halve the number of values per lane at
 // every exchange: 32 doubles take 32 exchanges instead of 192.  Bound by
 // instruction issue and the start of its short workgroups: 16^3x32 with 6
-// Gammas and 33 momenta 39 us a call with its wait (59 with one momentum a
+// Gammas and 33 momenta 37 us a call with its wait (58 with one momentum a
 // workgroup, which drew 13 TB/s from L2).
 // ONE: planes of up to BLK sites, one column a thread.
 template <int GB, int MB, bool ONE>
@@ -86,10 +86,10 @@ __global__ __launch_bounds__(BLK) void k_momproj(MomArgs a)
             double *u = ONE ? v : own;  // the column's sums with the phases of z
 #pragma unroll
             for (int k = 0; k < (ONE ? 0 : NV); ++k) u[k] = 0.0;
-            // two sites at a time; each term is rounded before it is added, so
-            // that one rounding in two sites has the size of the sum
+            // two sites at a time, their terms added up first: one rounding in
+            // two sites has the size of the sum
             int z = z0;
-#pragma unroll 1
+#pragma unroll 2
             for (; z + nz < a.Lz; z += 2 * nz) {
                 double2 l[2][GB];
 #pragma unroll
@@ -103,8 +103,8 @@ __global__ __launch_bounds__(BLK) void k_momproj(MomArgs a)
 #pragma unroll
                     for (int j = 0; j < GB; ++j) {
                         double *w = u + 2 * (m * 4 + j);
-                        w[0] += phase_re(p, l[0][j]) + phase_re(q, l[1][j]);
-                        w[1] += phase_im(p, l[0][j]) + phase_im(q, l[1][j]);
+                        w[0] += fma(q.x, l[1][j].x, fma(-q.y, l[1][j].y, phase_re(p, l[0][j])));
+                        w[1] += fma(q.x, l[1][j].y, fma(q.y, l[1][j].x, phase_im(p, l[0][j])));
                     }
                 }
             }
@@ -214,7 +214,7 @@ void launch_momproj(const double2 *L, double2 *Lp, const int *mom, int ngamma, i
     // up to 512 workgroups (two per CU) a momentum has one to itself: four in one
     // would leave CUs idle and, below four, compute repeats.  Calls with four and
     // with one: 24^3x16, 16 Gammas, 2 momenta 52.7 and 39.3 us, 16^3x32, 6 Gammas,
-    // 5 momenta 29.0 and 27.0; above, 16^3x32, 6 Gammas, 33 momenta 39 and 59
+    // 5 momenta 29.0 and 27.0; above, 16^3x32, 6 Gammas, 33 momenta 37 and 58
     const int mb = (long long)nt * ngr * nmom <= 512 ? 1 : MOMS;
     const size_t shm = (size_t)mb * (L4[0] + L4[1] + L4[2]) * sizeof(double2);
     for (a.k0 = 0; a.k0 < nmom; a.k0 += MCH) {
